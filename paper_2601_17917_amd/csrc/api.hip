@@ -194,10 +194,7 @@ int sdllm_plan_attention(const sdllm_attn_params* p, sdllm_attn_plan* plan) {
   if (rc != SDLLM_OK) return rc;
   if (!plan) return fail(SDLLM_ERR_INVALID_ARG, "plan_attention: plan is NULL");
   if (p->dtype == SDLLM_FP32) {
-    plan->kv_splits = 1; plan->rows_per_workgroup = 4;
-    plan->workgroups = ((p->K + p->n_keep + 3) / 4) * p->Hq * p->B;
-    plan->key_tiles_per_split = (p->prefix_len + p->K + p->n_keep + 63) / 64;
-    plan->workgroup_shape = 0; plan->ring_stages = 2;
+    sdllm::attention_f32_plan(*p, plan);
     return SDLLM_OK;
   }
   sdllm::AttnPlan pl = sdllm::plan_attention_bf16(*p);

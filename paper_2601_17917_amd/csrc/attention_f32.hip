@@ -1,14 +1,30 @@
 // fp32 attention over [prefix cache | block | gathered suffix] (paper Eq. 8 and the paragraph
-// after it).  Plain fp32 FMA arithmetic with an accurate exp: this is the correctness-grade
-// path (max-abs error <= 1e-5 against the fp64 definition), not the throughput path.
+// after it).  Full fp32 arithmetic on the matrix cores (v_mfma_f32_16x16x4_f32: products and sums in fp32)
+// with an accurate exp: the correctness-grade path (max-abs error <= 1e-5 against the fp64 definition).
 //
-// A workgroup = four query rows of one (batch, head), one wave per row.  Keys are visited in chunks of 64:
-// the workgroup brings the chunk's K and V rows into LDS with coalesced 16-byte loads (the four waves share
-// them), lane j scores key j of the chunk (dot product over D from LDS), the chunk's maximum and sum are formed
-// with wave reductions (online softmax), and for the output lane l owns columns l, l+64, ...
+// Work decomposition
+//   group = (batch, KV head): the g * Nq query rows that share its K/V are one list of "virtual rows", cut into
+//   16-row blocks.  A workgroup has NR x NK waves: wave (r, k) owns row block r of the workgroup and every NK-th
+//   16-key block of the sequence; the NK partial (O, m, l) of a row block merge through LDS in a fixed order.
+//   No wave shares an operand with another, so K and V go from global memory straight into registers in operand
+//   layout (a block's V during its Q K^T, the next block's K during its P V): no LDS and no barrier in the loop.  Waves of a workgroup
+//   that own different rows read the same key blocks at about the same time and meet in the L1.
+// Operand layout (lane: l16 = lane % 16, G = lane / 16; a 16x16x4 operand is ONE float per lane, row / column l16,
+// contraction index G)
+//   S^T = K Q^T   the contraction runs over d in any order, so the four instructions of 16-element slice s take the
+//                 components of one 16-byte load: d = 16 s + 4 G + j in instruction j.
+//   O^T = V^T P^T lane (q = l16, G) of the S^T accumulators holds keys 4 G + i, which is the B operand of instruction
+//                 i as it is; the A operand of output block (dg, j) is V[4 G + i][64 dg + 4 l16 + j], so one 16-byte
+//                 load of a V row serves the four blocks j.
+// What bounds it: the matrix pipe in principle (256 flop / cycle / CU in fp32, 157 TFLOP/s; two waves per SIMD cover each
+// other's softmax and load latency), at layer sizes the fixed parts of a short launch.  Measured, B2, 32 query / 8 KV heads
+// x 128, 64 query rows x 672 keys: 26 us (55 TFLOP/s, matrix pipe 40 % busy) against 276 us for one query row per wave
+// with fp32 FMAs out of LDS; B1, 4 heads x 64, 48 x 112: 7.2 against 17.5 us.
 #include "common.h"
 
 namespace sdllm {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 struct AttnF32Args {
   const float* q_block; const float* q_suffix;
@@ -17,112 +33,300 @@ struct AttnF32Args {
   const float* k_suffix; const float* v_suffix;
   const int32_t* keep_idx;
   float* out;
-  int B, Hq, Hkv, D, P, cap, K, S, n_keep;
+  int Hq, Hkv, g, D, P, cap, K, S, n_keep, Nq, Nkv, Rtot;
+  int n_groups, q_tiles, key_blocks;
+  int nr, nk;                     // waves of a workgroup: row blocks x key shares
+  int xcd_map;                    // workgroups of a group on one XCD (group count a good fit for 8)
   float scale;
 };
 
-constexpr int kF32MaxD = 256;
-constexpr int kF32Waves = 4;
+constexpr int kF32Rows = 16;      // query rows per wave
+constexpr int kF32Keys = 16;      // keys per block
 
-// row r of the pruned K/V sequence of KV head (b, kvh): pointer offset selection
-__device__ __forceinline__ const float* kv_row(const AttnF32Args& a, const float* cache, const float* block,
-                                               const float* suffix, int b, int kvh, int r) {
-  const long long bh = (long long)b * a.Hkv + kvh;
-  if (r < a.P) return cache + (bh * a.cap + r) * a.D;
-  r -= a.P;
-  if (r < a.K) return block + (bh * a.K + r) * a.D;
-  r -= a.K;
-  return suffix + (bh * a.S + a.keep_idx[r]) * a.D;
+// most waves of a workgroup: 8 (two per SIMD); 4 for 256-wide heads, whose operands and accumulators need the registers
+template <int NS> constexpr int f32_max_waves() { return NS <= 8 ? 8 : 4; }
+
+typedef const __attribute__((address_space(4))) int32_t* f32_const_i32_ptr;   // scalar loads
+
+// keep_idx of the first and last key of a block that lies wholly in the kept suffix, asked for one block ahead
+struct F32Ahead { int first, last; };
+
+__device__ __forceinline__ F32Ahead f32_ahead(const AttnF32Args& a, int blk) {
+  F32Ahead ka{0, 0};
+  const int s0 = blk * kF32Keys - a.P - a.K;
+  if (s0 >= 0 && s0 + kF32Keys <= a.n_keep) {
+    const f32_const_i32_ptr keep = (f32_const_i32_ptr)(uintptr_t)a.keep_idx;
+    ka.first = keep[s0]; ka.last = keep[s0 + kF32Keys - 1];
+  }
+  return ka;
 }
 
-// LDS: K chunk [64][D + 4] (the pad keeps 16-byte alignment and spreads the rows over the banks), V chunk [64][D]
-__host__ __device__ constexpr size_t f32_lds_bytes(int D) { return (size_t)64 * (2 * D + 4) * sizeof(float); }
+// Pointers into a tensor's three places.  Global address space by type: through a select or a null test the compiler
+// loses it, and generic loads are counted (and waited for) as LDS accesses too.  Three separate values wherever a row is
+// selected (in a struct the select becomes a table lookup in scratch memory).
+typedef const __attribute__((address_space(1))) float* f32_gptr;
+__device__ __forceinline__ f32x4 f32_load4(f32_gptr p) { return *reinterpret_cast<const __attribute__((address_space(1))) f32x4*>(p); }
 
-__global__ __launch_bounds__(64 * kF32Waves) void attention_f32_kernel(AttnF32Args a) {
-  __shared__ float q_s[kF32Waves][kF32MaxD];
-  extern __shared__ __attribute__((aligned(16))) float kv_s[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int Nq = a.K + a.n_keep, Nkv = a.P + a.K + a.n_keep;
-  const int qi = blockIdx.x * kF32Waves + wave;
-  const int hq = blockIdx.y, b = blockIdx.z;
-  const bool valid = qi < Nq;                // a wave without a row still helps to load and keeps the barriers
-  const int kvh = hq / (a.Hq / a.Hkv);
-  const int D = a.D, D4 = D / 4, KP = D + 4;
-  float* k_s = kv_s;
-  float* v_s = kv_s + 64 * KP;
-  const long long qbh = (long long)b * a.Hq + hq;
-  if (valid) {
-    const float* qrow = (qi < a.K) ? a.q_block + (qbh * a.K + qi) * D
-                                   : a.q_suffix + (qbh * a.S + a.keep_idx[qi - a.K]) * D;
-    for (int d = lane; d < D; d += 64) q_s[wave][d] = qrow[d];
-  }
+// Start of the 16 rows of key block `blk` where they are consecutive rows of one place (in the suffix: where keep_idx
+// maps them to consecutive rows), else nullptr.  Uniform.
+__device__ __forceinline__ f32_gptr f32_run(const AttnF32Args& a, f32_gptr tc, f32_gptr tb, f32_gptr ts, int blk, const F32Ahead& ka) {
+  const int r0 = blk * kF32Keys;
+  if (r0 + kF32Keys <= a.P) return tc + (long long)r0 * a.D;
+  if (r0 >= a.P && r0 + kF32Keys <= a.P + a.K) return tb + (long long)(r0 - a.P) * a.D;
+  if (ka.last - ka.first == kF32Keys - 1) return ts + (long long)ka.first * a.D;
+  return nullptr;
+}
 
-  constexpr int kCols = kF32MaxD / 64;       // output columns per lane
-  float o[kCols];
+// Any N rows (past the end: the last one, whose score is masked), by selects.  keep_idx is readable at entry 0 also
+// when nothing is kept (the launcher sees to it), so that the loads need no branch and travel together.
+template <int N>
+__device__ __forceinline__ void f32_rows(const AttnF32Args& a, f32_gptr tc, f32_gptr tb, f32_gptr ts, int row0, f32_gptr (&p)[N]) {
+  int row[N], kidx[N];
 #pragma unroll
-  for (int c = 0; c < kCols; ++c) o[c] = 0.f;
+  for (int i = 0; i < N; ++i) {
+    row[i] = min(row0 + i, a.Nkv - 1);
+    kidx[i] = a.keep_idx[max(row[i] - a.P - a.K, 0)];
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const bool in_c = row[i] < a.P, in_b = row[i] < a.P + a.K;
+    p[i] = (in_c ? tc : (in_b ? tb : ts)) + (long long)(in_c ? row[i] : (in_b ? row[i] - a.P : kidx[i])) * a.D;
+  }
+}
+
+// The loops below run over all NS slices whatever D is (no branches: the loads of a block travel together and the
+// wait counts stay exact); slices past D re-read the row's last elements, meet zeros of Q and are never stored.
+// K operands: lane (l16, G) takes d = 16 s + 4 G .. + 3 of key l16
+template <int NS>
+__device__ __forceinline__ void f32_load_k(const AttnF32Args& a, int l16, int G, f32_gptr tc, f32_gptr tb, f32_gptr ts, int blk,
+                                           const F32Ahead& ka, f32x4 (&k)[NS]) {
+  const f32_gptr run = f32_run(a, tc, tb, ts, blk, ka);
+  f32_gptr kp[1];
+  if (run != nullptr) kp[0] = run + l16 * a.D;
+  else f32_rows<1>(a, tc, tb, ts, blk * kF32Keys + l16, kp);
+#pragma unroll
+  for (int s = 0; s < NS; ++s) k[s] = f32_load4(kp[0] + min(16 * s + 4 * G, a.D - 4));
+}
+
+// V operands: lane (l16, G) takes d = 64 dg + 4 l16 .. + 3 of keys 4 G + i
+template <int NS>
+__device__ __forceinline__ void f32_load_v(const AttnF32Args& a, int l16, int G, f32_gptr tc, f32_gptr tb, f32_gptr ts, int blk,
+                                           const F32Ahead& ka, f32x4 (&v)[NS / 4][4]) {
+  const f32_gptr run = f32_run(a, tc, tb, ts, blk, ka);
+  f32_gptr vp[4];
+  if (run != nullptr) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) vp[i] = run + (4 * G + i) * a.D;
+  } else {
+    f32_rows<4>(a, tc, tb, ts, blk * kF32Keys + 4 * G, vp);
+  }
+#pragma unroll
+  for (int dg = 0; dg < NS / 4; ++dg)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[dg][i] = f32_load4(vp[i] + min(64 * dg + 4 * l16, a.D - 4));
+}
+
+// S^T of one key block, times the scale; keys past the end at -inf
+template <int NS>
+__device__ __forceinline__ f32x4 f32_scores(const AttnF32Args& a, int G, int blk, const f32x4 (&k)[NS], const f32x4 (&q)[NS]) {
+  f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[s][j], q[s][j], acc[j & 1], 0, 0, 0);
+  f32x4 sc = (acc[0] + acc[1]) * a.scale;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (blk * kF32Keys + 4 * G + i >= a.Nkv) sc[i] = -INFINITY;
+  return sc;
+}
+
+// Online softmax step and O^T += V^T P^T
+template <int NS>
+__device__ __forceinline__ void f32_accumulate(const AttnF32Args& a, const f32x4& sc, const f32x4 (&v)[NS / 4][4],
+                                               f32x4 (&o)[NS / 4][4], float& m, float& l) {
+  float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
+  const auto s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+  mx = fmaxf(__uint_as_float(s16[0]), __uint_as_float(s16[1]));
+  const auto s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+  mx = fmaxf(__uint_as_float(s32[0]), __uint_as_float(s32[1]));
+  const float m_new = fmaxf(m, mx);                // finite: a block holds at least one key
+  if (__builtin_amdgcn_ballot_w64(m_new != m) != 0) {      // uniform: some row's reference moves
+    const float corr = expf(m - m_new);            // first block: exp(-inf) = 0
+    l *= corr;
+#pragma unroll
+    for (int dg = 0; dg < NS / 4; ++dg)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[dg][j] *= corr;
+    m = m_new;
+  }
+  float p[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) p[i] = expf(sc[i] - m_new);
+  l += (p[0] + p[1]) + (p[2] + p[3]);              // this lane's keys; summed across the row's lanes at the end
+#pragma unroll
+  for (int dg = 0; dg < NS / 4; ++dg)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[dg][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[dg][i][j], p[i], o[dg][j], 0, 0, 0);
+}
+
+template <int NS>
+__global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) void attention_f32_kernel(AttnF32Args a) {
+  extern __shared__ __attribute__((aligned(16))) float f32_lds[];
+  const int lane = threadIdx.x & 63, l16 = lane & 15, G = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = wave % a.nr, wk = wave / a.nr;
+  // ---- which piece of work: with xcd_map the row tiles of a group sit on one XCD (its L2 holds the group's K/V)
+  int grp, qt;
+  if (a.xcd_map) {
+    const int xcd = blockIdx.x % kNumXCDs, slot = blockIdx.x / kNumXCDs;
+    grp = (slot / a.q_tiles) * kNumXCDs + xcd; qt = slot % a.q_tiles;
+  } else {
+    grp = blockIdx.x / a.q_tiles; qt = blockIdx.x % a.q_tiles;
+  }
+  if (grp >= a.n_groups) return;
+  const int b = grp / a.Hkv, kvh = grp - b * a.Hkv, D = a.D;
+  const long long bh = grp;
+  const f32_gptr kc = (f32_gptr)a.k_cache + bh * a.cap * D, vc = (f32_gptr)a.v_cache + bh * a.cap * D;
+  const f32_gptr kb = (f32_gptr)a.k_block + bh * a.K * D, vb = (f32_gptr)a.v_block + bh * a.K * D;
+  const f32_gptr ks = (f32_gptr)a.k_suffix + bh * a.S * D, vs = (f32_gptr)a.v_suffix + bh * a.S * D;
+
+  // ---- this wave's query rows; the first key block's K goes in flight while a kept row's keep_idx entry travels
+  const int R = (qt * a.nr + wr) * kF32Rows + l16;
+  const int Rc = min(R, a.Rtot - 1);
+  const int hl = Rc / a.Nq, qi = Rc - hl * a.Nq;
+  const long long qbh = (long long)b * a.Hq + (long long)kvh * a.g + hl;
+  const int q_keep = a.keep_idx[max(qi - a.K, 0)];
+  f32x4 k[NS], v[NS / 4][4];
+  F32Ahead ka = f32_ahead(a, wk);
+  f32_load_k<NS>(a, l16, G, kc, kb, ks, min(wk, a.key_blocks - 1), ka, k);
+  __builtin_amdgcn_sched_barrier(0);
+  const f32_gptr qp = qi < a.K ? (f32_gptr)a.q_block + (qbh * a.K + qi) * D : (f32_gptr)a.q_suffix + (qbh * a.S + q_keep) * D;
+  f32x4 q[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) q[s] = f32_load4(qp + min(16 * s + 4 * G, D - 4));
+  if (D < 16 * NS) {                               // uniform (the selects wait for the rows)
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+      if (16 * s + 4 * G >= D) q[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  f32x4 o[NS / 4][4];
+#pragma unroll
+  for (int dg = 0; dg < NS / 4; ++dg)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o[dg][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m = -INFINITY, l = 0.f;
 
-  for (int k0 = 0; k0 < Nkv; k0 += 64) {
-    const int nk = min(64, Nkv - k0);
-    __syncthreads();                         // the previous chunk is consumed (first trip: q_s is written)
-    for (int i = threadIdx.x; i < nk * D4; i += 64 * kF32Waves) {
-      const int j = i / D4, c4 = i - j * D4;
-      const float4 kk = reinterpret_cast<const float4*>(kv_row(a, a.k_cache, a.k_block, a.k_suffix, b, kvh, k0 + j))[c4];
-      const float4 vv = reinterpret_cast<const float4*>(kv_row(a, a.v_cache, a.v_block, a.v_suffix, b, kvh, k0 + j))[c4];
-      *reinterpret_cast<float4*>(k_s + j * KP + 4 * c4) = kk;
-      *reinterpret_cast<float4*>(v_s + j * D + 4 * c4) = vv;
-    }
-    __syncthreads();
-    if (!valid) continue;
-    float sc = -INFINITY;
-    if (lane < nk) {
-      const float4* kr = reinterpret_cast<const float4*>(k_s + lane * KP);
-      float acc = 0.f;
-      for (int d4 = 0; d4 < D4; ++d4) {
-        const float4 kk = kr[d4];
-        const float* qq = &q_s[wave][4 * d4];
-        acc = fmaf(qq[0], kk.x, acc); acc = fmaf(qq[1], kk.y, acc);
-        acc = fmaf(qq[2], kk.z, acc); acc = fmaf(qq[3], kk.w, acc);
-      }
-      sc = acc * a.scale;
-    }
-    float cmax = sc;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) cmax = fmaxf(cmax, __shfl_xor(cmax, off));
-    const float m_new = fmaxf(m, cmax);
-    const float corr = (m == -INFINITY) ? 0.f : expf(m - m_new);
-    const float p = (lane < nk) ? expf(sc - m_new) : 0.f;
-    float psum = p;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) psum += __shfl_xor(psum, off);
-    l = l * corr + psum;
-    m = m_new;
-#pragma unroll
-    for (int c = 0; c < kCols; ++c) o[c] *= corr;
-    for (int j = 0; j < nk; ++j) {
-      const float pj = __shfl(p, j);
-      const float* vr = v_s + j * D;
-#pragma unroll
-      for (int c = 0; c < kCols; ++c) {
-        const int d = lane + 64 * c;
-        if (d < D) o[c] = fmaf(pj, vr[d], o[c]);
-      }
-    }
+  // ---- key blocks wk, wk + nk, ...: a block's V travels during its scores, the next block's K during its P V
+  for (int blk = wk; blk < a.key_blocks; blk += a.nk) {
+    f32_load_v<NS>(a, l16, G, vc, vb, vs, blk, ka, v);
+    ka = f32_ahead(a, blk + a.nk);
+    const f32x4 sc = f32_scores<NS>(a, G, blk, k, q);
+    f32_load_k<NS>(a, l16, G, kc, kb, ks, min(blk + a.nk, a.key_blocks - 1), ka, k);     // (past the end: never used)
+    f32_accumulate<NS>(a, sc, v, o, m, l);
   }
-  if (!valid) return;
-  float* orow = a.out + (qbh * Nq + qi) * D;
-  const float inv = 1.0f / l;
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+
+  // ---- lane (q = l16, G) holds O[q][64 dg + 4 (4 G + i) + j]: for fixed i four consecutive elements
+  float* orow = a.out + (((long long)b * a.Hq + (long long)kvh * a.g) * a.Nq + R) * D;
+  if (a.nk == 1) {
+    const float inv = 1.0f / l;
+    if (R < a.Rtot) {
 #pragma unroll
-  for (int c = 0; c < kCols; ++c) {
-    const int d = lane + 64 * c;
-    if (d < D) orow[d] = o[c] * inv;
+      for (int dg = 0; dg < NS / 4; ++dg)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int d = 64 * dg + 16 * G + 4 * i;
+          if (d < D) *reinterpret_cast<f32x4*>(orow + d) = f32x4{o[dg][0][i], o[dg][1][i], o[dg][2][i], o[dg][3][i]} * inv;
+        }
+    }
+    return;
   }
+  const int nw = a.nr * a.nk;
+  f32x4* xo = reinterpret_cast<f32x4*>(f32_lds);                         // [wave][NS pieces][64 lanes]
+  float2* xml = reinterpret_cast<float2*>(f32_lds + nw * NS * 256);      // [wave][16 rows]
+#pragma unroll
+  for (int dg = 0; dg < NS / 4; ++dg)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      xo[(wave * NS + 4 * dg + i) * 64 + lane] = f32x4{o[dg][0][i], o[dg][1][i], o[dg][2][i], o[dg][3][i]};
+  if (G == 0) xml[wave * 16 + l16] = make_float2(m, l);
+  __syncthreads();
+  // the nk waves of a row block share its NS pieces; shares are merged in index order
+  float M = -INFINITY;
+  for (int k = 0; k < a.nk; ++k) M = fmaxf(M, xml[(k * a.nr + wr) * 16 + l16].x);
+  float L = 0.f;
+  for (int k = 0; k < a.nk; ++k) {
+    const float2 ml = xml[(k * a.nr + wr) * 16 + l16];
+    L += expf(ml.x - M) * ml.y;
+  }
+  const float inv = 1.0f / L;
+  for (int u = wk; u < NS; u += a.nk) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < a.nk; ++k) {
+      const int w = k * a.nr + wr;
+      acc += xo[(w * NS + u) * 64 + lane] * expf(xml[w * 16 + l16].x - M);
+    }
+    const int d = 64 * (u >> 2) + 16 * G + 4 * (u & 3);
+    if (R < a.Rtot && d < D) *reinterpret_cast<f32x4*>(orow + d) = acc * inv;
+  }
+}
+
+// Waves of a workgroup.  T = 16-row blocks of the call, aim = 8 waves per CU (two per SIMD).  Up to 256 blocks a
+// workgroup holds one block and splits the keys eight ways; with more blocks than CUs it takes 2, 4, 8 of them (they share
+// K/V in the L1) and splits the keys correspondingly less, as long as the last tile of a group is not mostly empty.
+struct F32Plan { int nr, nk, q_tiles, workgroups, xcd_map; };
+static F32Plan plan_attention_f32(const sdllm_attn_params& p) {
+  const int max_waves = p.D <= 128 ? f32_max_waves<8>() : f32_max_waves<16>();
+  const long long Rtot = (long long)(p.Hq / p.Hkv) * (p.K + p.n_keep);
+  const long long groups = (long long)p.B * p.Hkv;
+  const long long tiles = (Rtot + kF32Rows - 1) / kF32Rows;
+  const long long blocks = ((long long)p.prefix_len + p.K + p.n_keep + kF32Keys - 1) / kF32Keys;
+  F32Plan pl;
+  pl.nr = max_waves;
+  while (pl.nr > 1 && (pl.nr * (long long)kNumCUs > tiles * groups || (tiles + pl.nr - 1) / pl.nr * pl.nr * 8 > tiles * 9)) pl.nr >>= 1;
+  pl.nk = max_waves / pl.nr;
+  while (pl.nk > 1 && pl.nk / 2 >= blocks) pl.nk >>= 1;
+  pl.q_tiles = (int)((tiles + pl.nr - 1) / pl.nr);
+  const long long padded = (groups + kNumXCDs - 1) / kNumXCDs * kNumXCDs;
+  pl.xcd_map = padded * 4 <= groups * 5;
+  pl.workgroups = (int)((pl.xcd_map ? padded : groups) * pl.q_tiles);
+  return pl;
+}
+
+void attention_f32_plan(const sdllm_attn_params& p, sdllm_attn_plan* plan) {
+  const F32Plan pl = plan_attention_f32(p);
+  plan->kv_splits = 1; plan->rows_per_workgroup = kF32Rows * pl.nr; plan->workgroups = pl.workgroups;
+  plan->key_tiles_per_split = (p.prefix_len + p.K + p.n_keep + kF32Keys - 1) / kF32Keys;
+  plan->workgroup_shape = 0; plan->ring_stages = 2;
+}
+
+template <int NS> constexpr size_t f32_lds_bytes(int waves) { return (size_t)waves * (NS * 1024 + 16 * sizeof(float2)); }
+
+template <int NS>
+static hipError_t f32_opt_in() {
+  static LdsOptIn st;
+  return ensure_lds_opt_in(reinterpret_cast<const void*>(&attention_f32_kernel<NS>), f32_lds_bytes<NS>(f32_max_waves<NS>()), st);
 }
 
 hipError_t prepare_attention_f32() {
-  static LdsOptIn st;
-  return ensure_lds_opt_in(reinterpret_cast<const void*>(&attention_f32_kernel), f32_lds_bytes(kF32MaxD), st);
+  hipError_t e = f32_opt_in<4>();
+  if (e == hipSuccess) e = f32_opt_in<8>();
+  if (e == hipSuccess) e = f32_opt_in<16>();
+  return e;
+}
+
+template <int NS>
+static hipError_t f32_launch(const AttnF32Args& a, const F32Plan& pl, hipStream_t stream) {
+  const hipError_t e = f32_opt_in<NS>();
+  if (e != hipSuccess) return e;
+  const int waves = pl.nr * pl.nk;
+  hipLaunchKernelGGL(attention_f32_kernel<NS>, dim3(pl.workgroups), dim3(64 * waves), pl.nk > 1 ? f32_lds_bytes<NS>(waves) : 0,
+                     stream, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_attention_f32(const sdllm_attn_params& p,
@@ -131,21 +335,23 @@ hipError_t launch_attention_f32(const sdllm_attn_params& p,
                                 const void* k_block, const void* v_block,
                                 const void* k_suffix, const void* v_suffix,
                                 const int32_t* keep_idx, void* out, hipStream_t stream) {
+  const F32Plan pl = plan_attention_f32(p);
   AttnF32Args a;
   a.q_block = (const float*)q_block; a.q_suffix = (const float*)q_suffix;
   a.k_cache = (const float*)k_cache; a.v_cache = (const float*)v_cache;
   a.k_block = (const float*)k_block; a.v_block = (const float*)v_block;
   a.k_suffix = (const float*)k_suffix; a.v_suffix = (const float*)v_suffix;
-  a.keep_idx = keep_idx; a.out = (float*)out;
-  a.B = p.B; a.Hq = p.Hq; a.Hkv = p.Hkv; a.D = p.D; a.P = p.prefix_len; a.cap = p.prefix_cap;
+  // (f32_rows reads entry 0 without a branch when nothing is kept: any readable address will do)
+  a.keep_idx = p.n_keep > 0 ? keep_idx : (const int32_t*)q_block; a.out = (float*)out;
+  a.Hq = p.Hq; a.Hkv = p.Hkv; a.g = p.Hq / p.Hkv; a.D = p.D; a.P = p.prefix_len; a.cap = p.prefix_cap;
   a.K = p.K; a.S = p.S; a.n_keep = p.n_keep;
+  a.Nq = p.K + p.n_keep; a.Nkv = p.prefix_len + p.K + p.n_keep; a.Rtot = a.g * a.Nq;
+  a.n_groups = p.B * p.Hkv; a.q_tiles = pl.q_tiles; a.key_blocks = (a.Nkv + kF32Keys - 1) / kF32Keys;
+  a.nr = pl.nr; a.nk = pl.nk; a.xcd_map = pl.xcd_map;
   a.scale = p.scale > 0.f ? p.scale : 1.0f / sqrtf((float)p.D);
-  const int Nq = p.K + p.n_keep;
-  dim3 grid((Nq + kF32Waves - 1) / kF32Waves, p.Hq, p.B);
-  hipError_t e = prepare_attention_f32();     // opt-in to the LDS size of the largest head dim, once per device
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attention_f32_kernel, grid, dim3(64 * kF32Waves), f32_lds_bytes(p.D), stream, a);
-  return hipGetLastError();
+  if (p.D <= 64) return f32_launch<4>(a, pl, stream);
+  if (p.D <= 128) return f32_launch<8>(a, pl, stream);
+  return f32_launch<16>(a, pl, stream);
 }
 
 }  // namespace sdllm

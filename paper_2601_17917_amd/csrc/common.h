@@ -54,6 +54,7 @@ hipError_t launch_attention_bf16(const sdllm_attn_params& p, const AttnPlan& pla
                                  const void* k_suffix, const void* v_suffix,
                                  const int32_t* keep_idx, void* out, void* workspace, hipStream_t stream);
 
+void attention_f32_plan(const sdllm_attn_params& p, sdllm_attn_plan* plan);
 hipError_t launch_attention_f32(const sdllm_attn_params& p,
                                 const void* q_block, const void* q_suffix,
                                 const void* k_cache, const void* v_cache,

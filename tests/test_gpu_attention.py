@@ -71,6 +71,28 @@ def test_attention_fp32_shapes(gpu_lib, B, Hq, Hkv, D, P, cap, K, S, keep):
     assert np.abs(got - want).max() <= TOL["fp32"]
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,D,P,K,S,keep,nr", [
+    # one 16-row block per workgroup, the keys shared by up to eight waves: more waves than key blocks, a last block of
+    # one key, a full one, head widths off the 16- and 64-element grid
+    (1, 4, 4, 20, 14, 3, 0, (), 1),
+    (2, 4, 2, 80, 31, 17, 40, (0, 1, 5, 39), 1),
+    (1, 2, 1, 128, 112, 16, 64, tuple(range(16, 48)), 1),         # suffix blocks on consecutive rows
+    (1, 2, 1, 132, 50, 15, 33, tuple(range(0, 33, 2)), 1),        # ... on scattered rows; D > 128: four waves
+    (9, 1, 1, 64, 33, 5, 0, (), 1),                               # group count that does not fit the 8 chip parts
+    # two, four and eight row blocks per workgroup (from 512 row blocks on), the last tile of a group ragged
+    (16, 16, 16, 32, 10, 30, 0, (), 2),
+    (16, 64, 16, 64, 20, 16, 0, (), 4),
+    (16, 64, 16, 16, 7, 31, 1, (0,), 8),
+    (16, 64, 16, 144, 9, 16, 0, (), 4),
+])
+def test_attention_fp32_workgroup_shapes(gpu_lib, B, Hq, Hkv, D, P, K, S, keep, nr):
+    p = gpu_lib.attn_params(gpu_lib.FP32, B, Hq, Hkv, D, P, P + 3, K, S, len(keep))
+    assert gpu_lib.plan_attention(p).rows_per_workgroup == 16 * nr
+    t = wl.make_custom_attention_inputs("fp32", B, Hq, Hkv, D, P, P + 3, K, max(S, 1), keep, seed=D + P)
+    got = run_gpu(gpu_lib, t, P)
+    assert np.abs(got - oracle(t, P)).max() <= TOL["fp32"]
+
+
 @pytest.mark.parametrize("kv_splits", [0, 1, 2, 3])
 def test_attention_small_bf16(gpu_lib, kv_splits):
     w = wl.WORKLOADS["small_bf16"]             # GQA 4/2, P=107, K=32, s=33: ragged key and query tiles

@@ -3,7 +3,7 @@
 // (max, sum of exp, lowest argmax id) triples in registers; they are never written to memory.
 // The triples go to the same commit kernel as those of the streaming reduction over stored logits.
 //
-// One workgroup = one vocabulary tile (BN rows of W) x one chunk of BM masked rows, the whole of Hd.
+// One workgroup = one vocabulary tile (BN rows of W) x one chunk of masked rows (at most 256), the whole of Hd.
 //   * Masked rows are compacted inside the kernel (every workgroup scans the mask bytes), so the
 //     matrix cores only see rows that Eq. 4 asks for; a chunk beyond the masked count exits at once.
 //   * W is the streamed operand and has no reuse inside a workgroup: every wave owns WNB x 16
@@ -84,7 +84,6 @@ __device__ __forceinline__ int lm_masked_count(const LmHeadArgs& a, int* wsum) {
 
 template <int BM, int WNB, int PF_>
 struct LmShape {
-  static constexpr int JB = BM / 16;                        // 16-row blocks (B operands) per chunk
   static constexpr int BN = kLmWaves * WNB * 16;            // vocabulary rows per workgroup
   static constexpr int KC = kLmStageBytes / 2 / BM;         // hidden elements per row and stage
   static constexpr int KSTEPS = KC / 32;                    // MFMA k-steps per stage
@@ -92,7 +91,6 @@ struct LmShape {
   static constexpr int PF = PF_;                            // k-steps of W in flight per wave
   static constexpr int U = PF > KSTEPS ? PF / KSTEPS : 1;   // chunks per unrolled loop body (static ring slots)
   static constexpr int ROWS_PER_PASS = kLmThreads / PIECES; // rows one staging pass of the workgroup covers
-  static constexpr int NPASS = BM / ROWS_PER_PASS;          // 16-byte staging loads per thread and chunk
   static constexpr int MIN_WAVES = BM <= 64 ? 2 : 1;        // waves per SIMD the register budget must allow
   // The wide shapes are bound by the matrix pipe with one wave per SIMD.  Their 128 / 256 accumulator
   // registers sit in the accumulation half of the register file by construction (left to the register
@@ -101,7 +99,7 @@ struct LmShape {
   // stage (a chunk is complete one barrier before it is first read).
   static constexpr bool WIDE = BM >= 128;
   static constexpr int NST = WIDE ? 3 : 2;
-  static constexpr int DB = 4;
+  static constexpr int DB = 8;
   static constexpr int HDEPTH = KSTEPS >= 4 ? 1 : 4 / KSTEPS;   // chunks a hidden chunk waits in registers (wide)
   static_assert((PIECES == 8 || PIECES % 16 == 0) && kLmThreads % PIECES == 0, "shape");
   static_assert((KSTEPS * U) % PF == 0 && (U == 1 || U % 2 == 0) && (!WIDE || U % HDEPTH == 0), "ring");
@@ -125,54 +123,21 @@ __device__ __forceinline__ void mfma_acc(f32x4& acc, const bf16x8& a, const bf16
   else acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
 }
 
+// One (vocabulary tile, row chunk) of lm_head_rows_kernel: JB 16-row blocks of positions.
 // PACKED: W is the packed image (a lane's operand pieces of consecutive k-steps are 1 KB apart, a wave's load is
 // one contiguous kilobyte that no other load touches: nontemporal)
-template <int BM, int WNB, int PF_, bool PACKED>
-__global__ __launch_bounds__(kLmThreads, (LmShape<BM, WNB, PF_>::MIN_WAVES)) void lm_head_rows_kernel(LmHeadArgs a) {
+// Bound by the matrix pipe as one wave per SIMD can keep it busy, and by the stream of W under it.  Per call over
+// 126464 x 4096, packed W, full 256-row chunks and loads issued in bursts before / as it is now:
+//   160 masked positions 279 / 204 us, 256: 299 / 284, 282: 510 / 373, 384: 509 / 405, 512: 539 / 506 (1.05 PFLOP/s)
+// and row-major W: 160 positions 315 / 251 us, 256: 306 / 304, 282: 549 / 442, 512: 558 / 532.
+template <int BM, int WNB, int PF_, bool PACKED, int JB>
+__device__ __forceinline__ void lm_head_rows_tile(const LmHeadArgs& a, unsigned char* stage, const int* row_of,
+                                                  Partial* red, int tile) {
   using S = LmShape<BM, WNB, PF_>;
-  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  unsigned char* stage = lds_raw;                                          // NST x kLmStageBytes
-  int* row_of = reinterpret_cast<int*>(lds_raw + S::NST * kLmStageBytes);  // BM compacted row ids (-1 = none)
-  Partial* red = reinterpret_cast<Partial*>(row_of + BM);                  // [waves][BM]
-  __shared__ int wsum[kLmWaves];
-
+  static_assert(JB % 2 == 0 && JB * 16 <= BM, "whole staging passes, rows that the LDS layout holds");
+  constexpr int NPASS = JB * 16 / S::ROWS_PER_PASS;            // 16-byte staging loads per thread and chunk
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // ---- the masked count decides how many row chunks there are
-  const int total = lm_masked_count(a, wsum);
-  if (total < max(a.min_masked, 1)) return;        // another shape's launch has this call, or nothing is masked
-  const int nact = (total + BM - 1) / BM;          // <= a.nchunk, since total <= rows_total
-  // ---- workgroup -> (vocabulary tile, row chunk): chunks of a tile share id mod 8 (the XCD) and are adjacent
-  // in dispatch order.  Only chunks that hold rows get workgroup ids: the idle workgroups of a grid sized for
-  // B x K rows are its last ones (interleaved with the working ones they kept half of the chip idle: 256 of
-  // 512 positions masked took 497 us, not the 320 us of 256 of 256).
-  const int slot = blockIdx.x >> 3;
-  const int tile = (slot / nact) * kNumXCDs + (blockIdx.x & 7);
-  const int chunk = slot % nact;
-  if (tile >= a.ntile) return;
-
-  // ---- compact the masked rows; this workgroup takes compacted rows [lo, lo + BM)
-  const int lo = chunk * BM;
-  int running = 0;
-  for (int base = 0; base < a.rows_total; base += kLmThreads) {
-    const int i = base + tid;
-    const bool f = i < a.rows_total && a.masked[i] != 0;
-    const unsigned long long bal = __ballot(f);
-    const int rank = __popcll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0) wsum[wave] = __popcll(bal);
-    __syncthreads();
-    int pre = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < kLmWaves; ++w) { const int c = wsum[w]; pre += (w < wave) ? c : 0; tot += c; }
-    const int ci = running + pre + rank - lo;
-    if (f && ci >= 0 && ci < BM) row_of[ci] = i;
-    running += tot;
-    __syncthreads();
-    if (running >= lo + BM) break;                 // uniform: the chunk is full
-  }
-  const int n_valid = min(running - lo, BM);       // uniform, >= 1 because chunk < nact
-  if (tid < BM && tid >= n_valid) row_of[tid] = -1;
-  __syncthreads();
 
   // ---- operand addressing
   const int NK = a.Hd / 32;                                    // k-steps
@@ -181,12 +146,10 @@ __global__ __launch_bounds__(kLmThreads, (LmShape<BM, WNB, PF_>::MIN_WAVES)) voi
   // every workgroup walks the chunks of Hd in its own rotation, so that the workgroups resident at one
   // time do not all ask for the same columns of W at once
   const int c0 = tile % NCH;
-  auto kstep_at = [&](int t) {                                 // k-step at position t of this workgroup's walk
-    const int cc = t / S::KSTEPS, ss = t - cc * S::KSTEPS;
-    const int ch = (cc + c0) % NCH;
-    return min(ch * S::KSTEPS + ss, NK - 1);
-  };
   auto chunk_at = [&](int c) { int ch = c + c0; ch -= (ch >= NCH) ? NCH : 0; return ch; };   // c < NCH
+  auto kstep_at = [&](int c, int ss) {                         // k-step ss of the chunk at walk position c; past the
+    return min(chunk_at(min(c, NCH - 1)) * S::KSTEPS + ss, NK - 1);   // end any valid one
+  };
   const uint16_t* wrow[WNB];                                   // this lane's operand piece of k-step 0
   constexpr int wks = PACKED ? 512 : 32;                       // elements from one k-step's piece to the next
 #pragma unroll
@@ -201,10 +164,10 @@ __global__ __launch_bounds__(kLmThreads, (LmShape<BM, WNB, PF_>::MIN_WAVES)) voi
   }
   // staging: this thread moves piece `pc` of rows srow0 + ROWS_PER_PASS * i
   const int pc = tid % S::PIECES, srow0 = tid / S::PIECES;
-  unsigned hoff[S::NPASS];       // element offset of the thread's rows
-  unsigned soff[S::NPASS];       // byte offset inside a stage
+  unsigned hoff[NPASS];          // element offset of the thread's rows
+  unsigned soff[NPASS];          // byte offset inside a stage
 #pragma unroll
-  for (int i = 0; i < S::NPASS; ++i) {
+  for (int i = 0; i < NPASS; ++i) {
     const int r = srow0 + S::ROWS_PER_PASS * i;
     hoff[i] = (unsigned)((long long)max(row_of[r], 0) * a.ld_h);
     soff[i] = (unsigned)(r * S::KC * 2 + (S::swz(r, pc) << 4));
@@ -212,18 +175,23 @@ __global__ __launch_bounds__(kLmThreads, (LmShape<BM, WNB, PF_>::MIN_WAVES)) voi
   // B-operand read of 16-row block jb, k-step ks: row jb * 16 + l16, piece 4 ks + q
   const unsigned boff = (unsigned)(l16 * S::KC * 2);
 
-  f32x4 acc[WNB][S::JB];
+  f32x4 acc[WNB][JB];
 #pragma unroll
   for (int ib = 0; ib < WNB; ++ib)
 #pragma unroll
-    for (int jb = 0; jb < S::JB; ++jb) acc[ib][jb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int jb = 0; jb < JB; ++jb) acc[ib][jb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // ---- prologue: first W k-steps in flight, first hidden chunk(s) into LDS
   bf16x8 abuf[S::PF][WNB];
+  auto load_w_first = [&](int s0, int s1) {
 #pragma unroll
-  for (int s = 0; s < S::PF; ++s)
+    for (int s = 0; s < S::PF; ++s)
 #pragma unroll
-    for (int ib = 0; ib < WNB; ++ib) abuf[s][ib] = load_w<PACKED>(wrow[ib] + wks * kstep_at(s));
+      for (int ib = 0; ib < WNB; ++ib)
+        if (s >= s0 && s < s1)
+          abuf[s][ib] = load_w<PACKED>(wrow[ib] + (long long)wks * kstep_at(s / S::KSTEPS, s % S::KSTEPS));
+  };
+  load_w_first(0, S::PF - S::KSTEPS);
   // A chunk's pieces past Hd are staged as zeros and its k-steps past Hd are computed like the others
   // (finite W times zero adds nothing): the loop body has no branch, so the compiler's wait counters
   // see one straight line and keep the W loads PF steps ahead.
@@ -232,7 +200,7 @@ __global__ __launch_bounds__(kLmThreads, (LmShape<BM, WNB, PF_>::MIN_WAVES)) voi
     const unsigned k = (unsigned)(chunk_at(c < NCH ? c : 0) * S::KC) + 8u * pc;
     const bool keep = c < NCH && k < (unsigned)a.Hd;
 #pragma unroll
-    for (int i = 0; i < S::NPASS; ++i) {
+    for (int i = 0; i < NPASS; ++i) {
       const u32x4 v = *reinterpret_cast<const u32x4*>(a.hidden + (hoff[i] + min(k, klast)));
       *reinterpret_cast<u32x4*>(dst + soff[i]) = keep ? v : u32x4{0u, 0u, 0u, 0u};
     }
@@ -245,8 +213,9 @@ __global__ __launch_bounds__(kLmThreads, (LmShape<BM, WNB, PF_>::MIN_WAVES)) voi
   const int NCHU = (NCH + S::U - 1) / S::U * S::U;      // chunks past NCH see zeros
   if constexpr (S::WIDE) {
     // ---- main loop, wide shapes: three LDS stages (read c, already complete c + 1, being written c + 2)
-    constexpr int CH = S::KSTEPS * S::JB;               // B operands per chunk
-    static_assert(CH % S::DB == 0, "B ring");
+    constexpr int CH = S::KSTEPS * JB;                  // B operands per chunk
+    static_assert(S::U * CH % S::DB == 0 && S::DB <= CH, "B ring");
+    static_assert(S::KSTEPS > 1, "staging loads and stores in different k-steps");
     unsigned pv[S::KSTEPS];                             // per-lane part of a B-operand address, by k-step
 #pragma unroll
     for (int ks = 0; ks < S::KSTEPS; ++ks) pv[ks] = boff + (unsigned)(S::swz(l16, 4 * ks + q) << 4);
@@ -256,18 +225,18 @@ __global__ __launch_bounds__(kLmThreads, (LmShape<BM, WNB, PF_>::MIN_WAVES)) voi
     unsigned cur_off = 0, nxt_off = kLmStageBytes, wr_off = 2 * kLmStageBytes;    // uniform
     bf16x8 bq[S::DB];
 #pragma unroll
-    for (int d = 0; d < S::DB; ++d) bq[d] = read_b(cur_off, d / S::JB, d % S::JB);
+    for (int d = 0; d < S::DB; ++d) bq[d] = read_b(cur_off, d / JB, d % JB);
     // Loads return in issue order, so waiting for a young load also waits for every older one: a hidden
     // chunk that is consumed at the end of the chunk it was asked for in would drain the W ring down to
     // the loads of that chunk, however far ahead the ring runs.  The hidden chunks therefore travel HD
     // chunks ahead in registers, so that nothing younger than about PF k-steps is ever waited for.
     constexpr int HD = S::HDEPTH;                       // chunks a hidden chunk waits in registers
-    u32x4 hreg[HD][S::NPASS];
-    auto load_hidden = [&](int c, u32x4 (&dst)[S::NPASS]) {      // chunk at walk position c (zeros past the end)
+    u32x4 hreg[HD][NPASS];
+    auto load_hidden = [&](int c, u32x4 (&dst)[NPASS]) {      // chunk at walk position c (zeros past the end)
       const unsigned k = (unsigned)(chunk_at(c < NCH ? c : 0) * S::KC) + 8u * pc;
       const unsigned kc = min(k, klast);
 #pragma unroll
-      for (int i = 0; i < S::NPASS; ++i) dst[i] = *reinterpret_cast<const u32x4*>(a.hidden + (hoff[i] + kc));
+      for (int i = 0; i < NPASS; ++i) dst[i] = *reinterpret_cast<const u32x4*>(a.hidden + (hoff[i] + kc));
     };
     auto keep_mask = [&](int c) -> unsigned {
       const unsigned k = (unsigned)(chunk_at(c < NCH ? c : 0) * S::KC) + 8u * pc;
@@ -275,40 +244,54 @@ __global__ __launch_bounds__(kLmThreads, (LmShape<BM, WNB, PF_>::MIN_WAVES)) voi
     };
 #pragma unroll
     for (int d = 1; d < HD; ++d) load_hidden(1 + d, hreg[d % HD]);     // chunks 2 .. HD: as if asked for earlier
+    // the last chunk's worth of W after them, the order that the loop leaves: with the hidden chunk as the youngest
+    // load the wait counts of the first chunk of every trip would cover for that (9 instead of 20)
+    __builtin_amdgcn_sched_barrier(0);
+    load_w_first(S::PF - S::KSTEPS, S::PF);
     for (int cb = 0; cb < NCHU; cb += S::U) {
 #pragma unroll
       for (int uu = 0; uu < S::U; ++uu) {
         const int c = cb + uu;
-        // asked for now: chunk c + 1 + HD; written to LDS at the end of this chunk: chunk c + 2
-        load_hidden(c + 1 + HD, hreg[uu % HD]);
-        __builtin_amdgcn_sched_barrier(0);
+        // One wave per SIMD: whatever is issued between two matrix instructions beyond their 16 cycles leaves the pipe
+        // idle, so a chunk's other work is dealt out among them, one piece per group of WNB: in the first k-step the
+        // loads of hidden chunk c + 1 + HD, in the last the LDS stores of chunk c + 2 (asked for HD - 1 chunks ago)
+        // into the free stage, behind a k-step's last group its operands' successors.
+        const unsigned kh = (unsigned)(chunk_at(c + 1 + HD < NCH ? c + 1 + HD : 0) * S::KC) + 8u * pc;
+        const unsigned khc = min(kh, klast);
+        // pieces past Hd become zeros by masking, not by a select: a select would let the compiler turn the loads
+        // into conditional ones and sink them down to the stores
+        const unsigned keep = keep_mask(c + 2);
 #pragma unroll
         for (int ks = 0; ks < S::KSTEPS; ++ks) {
-          const int g = c * S::KSTEPS + ks;
           const int slot_a = (uu * S::KSTEPS + ks) % S::PF;
-          bf16x8 aop[WNB];
+          const int gn = uu * S::KSTEPS + ks + S::PF;   // relative to the trip's first k-step
+          const long long wnext = (long long)wks * kstep_at(cb + gn / S::KSTEPS, gn % S::KSTEPS);
 #pragma unroll
-          for (int ib = 0; ib < WNB; ++ib) aop[ib] = abuf[slot_a][ib];
+          for (int jb = 0; jb < JB; ++jb) {
+            const int t = ks * JB + jb, tn = t + S::DB;
+            const int slot_b = (uu * CH + t) % S::DB;
+            const bf16x8 bop = bq[slot_b];
+            bq[slot_b] = tn < CH ? read_b(cur_off, tn / JB, tn % JB)
+                                 : read_b(nxt_off, (tn - CH) / JB, (tn - CH) % JB);
+            if (ks == 0 && jb < NPASS)
+              hreg[uu % HD][jb] = *reinterpret_cast<const u32x4*>(a.hidden + (hoff[jb] + khc));
+            if (ks == S::KSTEPS - 1 && jb < NPASS)
+              *reinterpret_cast<u32x4*>(stage + wr_off + soff[jb]) = hreg[(uu + 1) % HD][jb] & u32x4{keep, keep, keep, keep};
 #pragma unroll
-          for (int ib = 0; ib < WNB; ++ib) abuf[slot_a][ib] = load_w<PACKED>(wrow[ib] + wks * kstep_at(g + S::PF));
-#pragma unroll
-          for (int jb = 0; jb < S::JB; ++jb) {
-            const int t = ks * S::JB + jb, tn = t + S::DB;
-            const bf16x8 bop = bq[t % S::DB];
-            bq[t % S::DB] = tn < CH ? read_b(cur_off, tn / S::JB, tn % S::JB)
-                                    : read_b(nxt_off, (tn - CH) / S::JB, (tn - CH) % S::JB);
-#pragma unroll
-            for (int ib = 0; ib < WNB; ++ib) mfma_acc<true>(acc[ib][jb], aop[ib], bop);
+            for (int ib = 0; ib < WNB; ++ib) {
+              mfma_acc<true>(acc[ib][jb], abuf[slot_a][ib], bop);
+              // The last group has read the operand: the load PF steps ahead goes into the same registers.  (Asked for
+              // before the matrix instructions it needed registers of its own, and the copies that rotate those into
+              // place at the loop's end waited for every load in flight, once per trip.)
+              if (jb == JB - 1) {
+                __builtin_amdgcn_sched_barrier(0);
+                abuf[slot_a][ib] = load_w<PACKED>(wrow[ib] + wnext);
+                __builtin_amdgcn_sched_barrier(0);
+              }
+            }
             __builtin_amdgcn_sched_barrier(0);          // keep the ring's distance as written
           }
         }
-        // chunk c + 2 (asked for HD - 1 chunks ago) into the free stage.  Pieces past Hd become zeros by
-        // masking, not by a select: a select would let the compiler turn the loads into conditional ones
-        // and sink them down here
-        const unsigned keep = keep_mask(c + 2);
-#pragma unroll
-        for (int i = 0; i < S::NPASS; ++i)
-          *reinterpret_cast<u32x4*>(stage + wr_off + soff[i]) = hreg[(uu + 1) % HD][i] & u32x4{keep, keep, keep, keep};
         __syncthreads();
         const unsigned tmp = cur_off; cur_off = nxt_off; nxt_off = wr_off; wr_off = tmp;
       }
@@ -321,7 +304,7 @@ __global__ __launch_bounds__(kLmThreads, (LmShape<BM, WNB, PF_>::MIN_WAVES)) voi
   // ---- row reduction of the tile: in-lane over this lane's vocabulary ids (ascending), then over the
   // four lane groups, then over the waves
 #pragma unroll
-  for (int jb = 0; jb < S::JB; ++jb) {
+  for (int jb = 0; jb < JB; ++jb) {
     float m = kNegBig; int idx = 0x7fffffff;
 #pragma unroll
     for (int ib = 0; ib < WNB; ++ib)
@@ -347,7 +330,7 @@ __global__ __launch_bounds__(kLmThreads, (LmShape<BM, WNB, PF_>::MIN_WAVES)) voi
     if (q == 0) red[wave * BM + jb * 16 + l16] = Partial{m, s, idx};
   }
   __syncthreads();
-  if (tid < BM && row_of[tid] >= 0) {
+  if (tid < JB * 16 && row_of[tid] >= 0) {
     Partial p = red[tid];
 #pragma unroll
     for (int w = 1; w < kLmWaves; ++w) {
@@ -355,6 +338,66 @@ __global__ __launch_bounds__(kLmThreads, (LmShape<BM, WNB, PF_>::MIN_WAVES)) voi
       merge_partial(p.m, p.s, p.idx, p2.m, p2.s, p2.idx);
     }
     store_partial(a, row_of[tid], tile, p);
+  }
+}
+
+template <int BM, int WNB, int PF_, bool PACKED>
+__global__ __launch_bounds__(kLmThreads, (LmShape<BM, WNB, PF_>::MIN_WAVES)) void lm_head_rows_kernel(LmHeadArgs a) {
+  using S = LmShape<BM, WNB, PF_>;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
+  unsigned char* stage = lds_raw;                                          // NST x kLmStageBytes
+  int* row_of = reinterpret_cast<int*>(lds_raw + S::NST * kLmStageBytes);  // BM compacted row ids (-1 = none)
+  Partial* red = reinterpret_cast<Partial*>(row_of + BM);                  // [waves][BM]
+  __shared__ int wsum[kLmWaves];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // ---- the masked count decides how many row chunks there are
+  const int total = lm_masked_count(a, wsum);
+  if (total < max(a.min_masked, 1)) return;        // another shape's launch has this call, or nothing is masked
+  // The rows go to as few chunks as their number allows, spread evenly and rounded up to 32: a chunk's matrix
+  // instructions follow from the 16-row blocks it is built for, so 282 rows as 160 + 122 cost 320 rows' worth and not
+  // the 512 of two full chunks (with the count above 128, an even share always exceeds 128 rows).
+  const int share = (total + BM - 1) / BM;
+  const int bm = (((total + share - 1) / share) + 31) & ~31;         // 160, 192, 224 or 256 rows
+  const int nact = (total + bm - 1) / bm;          // <= share <= a.nchunk, since total <= rows_total
+  // ---- workgroup -> (vocabulary tile, row chunk): chunks of a tile share id mod 8 (the XCD) and are adjacent
+  // in dispatch order.  Only chunks that hold rows get workgroup ids: the idle workgroups of a grid sized for
+  // B x K rows are its last ones (interleaved with the working ones they kept half of the chip idle: 256 of
+  // 512 positions masked took 497 us, not the 320 us of 256 of 256).
+  const int slot = blockIdx.x >> 3;
+  const int tile = (slot / nact) * kNumXCDs + (blockIdx.x & 7);
+  const int chunk = slot % nact;
+  if (tile >= a.ntile) return;
+
+  // ---- compact the masked rows; this workgroup takes compacted rows [lo, lo + bm)
+  const int lo = chunk * bm;
+  int running = 0;
+  for (int base = 0; base < a.rows_total; base += kLmThreads) {
+    const int i = base + tid;
+    const bool f = i < a.rows_total && a.masked[i] != 0;
+    const unsigned long long bal = __ballot(f);
+    const int rank = __popcll(bal & ((1ull << lane) - 1ull));
+    if (lane == 0) wsum[wave] = __popcll(bal);
+    __syncthreads();
+    int pre = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < kLmWaves; ++w) { const int c = wsum[w]; pre += (w < wave) ? c : 0; tot += c; }
+    const int ci = running + pre + rank - lo;
+    if (f && ci >= 0 && ci < bm) row_of[ci] = i;
+    running += tot;
+    __syncthreads();
+    if (running >= lo + bm) break;                 // uniform: the chunk is full
+  }
+  const int n_valid = min(running - lo, bm);       // uniform, >= 1 because chunk < nact
+  if (tid < bm && tid >= n_valid) row_of[tid] = -1;
+  __syncthreads();
+
+  switch (bm / 32) {                               // uniform
+    case 8: lm_head_rows_tile<BM, WNB, PF_, PACKED, 16>(a, stage, row_of, red, tile); break;
+    case 7: lm_head_rows_tile<BM, WNB, PF_, PACKED, 14>(a, stage, row_of, red, tile); break;
+    case 6: lm_head_rows_tile<BM, WNB, PF_, PACKED, 12>(a, stage, row_of, red, tile); break;
+    default: lm_head_rows_tile<BM, WNB, PF_, PACKED, 10>(a, stage, row_of, red, tile); break;
   }
 }
 

@@ -187,6 +187,21 @@ def test_lm_head_shape_follows_the_masked_count(gpu_lib, B, K, n_masked, packed)
     assert skipped <= 1
 
 
+@pytest.mark.parametrize("n_masked", [160, 161, 192, 193, 224, 225, 256, 257, 320, 321, 448, 512, 513, 576])
+@pytest.mark.parametrize("packed", [False, True])
+def test_lm_head_row_chunks_at_their_edges(gpu_lib, n_masked, packed):
+    """More than 128 masked positions: chunks of 160, 192, 224 and 256 rows, one to three of them, full and not."""
+    B, K, Hd, V = 9, 64, 160, 1100
+    h, W, tokens, masked, hd, Wd = _host_case(B, K, Hd, V, seed=n_masked, frac=0.0)
+    flat = np.random.Generator(np.random.Philox(key=n_masked)).permutation(B * K)[:n_masked]
+    masked.reshape(-1)[flat] = 1
+    tokens.reshape(-1)[flat] = wl.MASK_TOKEN
+    got = run_gpu(gpu_lib, hd, Wd, tokens, masked, 0.7, 0.3, packed=packed)
+    want = _oracle(h, W, tokens, masked, 0.7, 0.3)
+    n_gap, n_band, skipped = compare(got, want, tokens, masked)
+    assert skipped <= 1
+
+
 @pytest.mark.parametrize("B,K,Hd,V,ld_h,ld_w", [(2, 16, 64, 200, 72, 80), (2, 32, 320, 1000, 328, 384),
                                                  (4, 32, 320, 1000, 328, 384),
                                                  (3, 32, 320, 1000, 328, 384)])

@@ -26,6 +26,23 @@ __device__ __forceinline__ void merge_partial(float& m, float& s, int& i, float 
   m = M;
 }
 
+// The same lane of the wave's four rows of 16 combined, by the two row swaps; every lane ends with the result.
+template <typename T, typename F>
+__device__ __forceinline__ T row_allreduce(T v, F op) {
+  static_assert(sizeof(T) == 4, "32-bit values");
+  // the two swaps exchange rows 1 <-> 0, 3 <-> 2 and then the halves between their two operands (the same value
+  // twice here); the results are copied into scalars before the bit casts (a bit cast applied to a vector element
+  // expression reads element 0 with this compiler)
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto r16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned a0 = r16[0], a1 = r16[1];
+  v = op(__builtin_bit_cast(T, a0), __builtin_bit_cast(T, a1));
+  const unsigned w = __builtin_bit_cast(unsigned, v);
+  const auto r32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  const unsigned b0 = r32[0], b1 = r32[1];
+  return op(__builtin_bit_cast(T, b0), __builtin_bit_cast(T, b1));
+}
+
 // Wave-wide reductions on the vector ALU's own lane network (DPP row operations inside each row of 16 lanes, then
 // the two row swaps): ~10 cycles per step where a shuffle through the LDS crossbar is a memory-pipe round trip.
 // Every lane ends with the result.
@@ -40,17 +57,7 @@ __device__ __forceinline__ T wave_allreduce(T v, F op) {
   v = op(v, dpp(v, std::integral_constant<int, 0x4E>{}));    // quad_perm [2,3,0,1]
   v = op(v, dpp(v, std::integral_constant<int, 0x141>{}));   // row_half_mirror: the other quad of each 8
   v = op(v, dpp(v, std::integral_constant<int, 0x140>{}));   // row_mirror: the other half of each row of 16
-  // the two swaps exchange rows 1 <-> 0, 3 <-> 2 and then the halves between their two operands (the same value
-  // twice here); the results are copied into scalars before the bit casts (a bit cast applied to a vector element
-  // expression reads element 0 with this compiler)
-  const unsigned u = __builtin_bit_cast(unsigned, v);
-  const auto r16 = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const unsigned a0 = r16[0], a1 = r16[1];
-  v = op(__builtin_bit_cast(T, a0), __builtin_bit_cast(T, a1));
-  const unsigned w = __builtin_bit_cast(unsigned, v);
-  const auto r32 = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-  const unsigned b0 = r32[0], b1 = r32[1];
-  return op(__builtin_bit_cast(T, b0), __builtin_bit_cast(T, b1));
+  return row_allreduce(v, op);
 }
 
 // The value a partner lane holds, for a butterfly over groups of 2^(LEVEL+1) adjacent lanes: level 0 / 1 pair lane i

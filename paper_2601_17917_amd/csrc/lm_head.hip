@@ -128,8 +128,8 @@ __device__ __forceinline__ void mfma_acc(f32x4& acc, const bf16x8& a, const bf16
 // one contiguous kilobyte that no other load touches: nontemporal)
 // Bound by the matrix pipe as one wave per SIMD can keep it busy, and by the stream of W under it.  Per call over
 // 126464 x 4096, packed W, full 256-row chunks and loads issued in bursts before / as it is now:
-//   160 masked positions 279 / 204 us, 256: 299 / 284, 282: 510 / 373, 384: 509 / 405, 512: 539 / 506 (1.05 PFLOP/s)
-// and row-major W: 160 positions 315 / 251 us, 256: 306 / 304, 282: 549 / 442, 512: 558 / 532.
+//   160 masked positions 279 / 203 us, 256: 299 / 270, 282: 510 / 350, 384: 509 / 405, 512: 539 / 496 (1.07 PFLOP/s)
+// and row-major W: 160 positions 315 / 245 us, 256: 306 / 289, 282: 549 / 420, 512: 558 / 520.
 template <int BM, int WNB, int PF_, bool PACKED, int JB>
 __device__ __forceinline__ void lm_head_rows_tile(const LmHeadArgs& a, unsigned char* stage, const int* row_of,
                                                   Partial* red, int tile) {

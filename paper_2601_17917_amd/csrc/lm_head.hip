@@ -116,11 +116,16 @@ __device__ __forceinline__ bf16x8 load_w(const uint16_t* p) {
   else return *reinterpret_cast<const bf16x8*>(p);
 }
 
-// acc += A B, with the accumulator either left to the compiler or pinned to the accumulation registers
-template <bool ACC_IN_AGPR>
+// acc += A B with the accumulator pinned to the accumulation registers.  The compiler does not see a matrix instruction
+// inside the asm statement and puts no wait states behind it.  Between matrix instructions none are needed; the LAST one
+// before other instructions read the accumulators brings its own, the 8 that the compiler itself puts between this
+// instruction and a read of its result.  They are part of the statement because a wait by itself behind the loop holds
+// nothing back: the register copies that the compiler makes between the loop and the first read pass it, with or without
+// a memory clobber, and also when the accumulators are its operands.
+template <bool WAIT>
 __device__ __forceinline__ void mfma_acc(f32x4& acc, const bf16x8& a, const bf16x8& b) {
-  if constexpr (ACC_IN_AGPR) asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-  else acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0);
+  if constexpr (WAIT) asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\ts_nop 7" : "+a"(acc) : "v"(a), "v"(b));
+  else asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 
 // One (vocabulary tile, row chunk) of lm_head_rows_kernel: JB 16-row blocks of positions.
@@ -279,7 +284,10 @@ __device__ __forceinline__ void lm_head_rows_tile(const LmHeadArgs& a, unsigned 
               *reinterpret_cast<u32x4*>(stage + wr_off + soff[jb]) = hreg[(uu + 1) % HD][jb] & u32x4{keep, keep, keep, keep};
 #pragma unroll
             for (int ib = 0; ib < WNB; ++ib) {
-              mfma_acc<true>(acc[ib][jb], abuf[slot_a][ib], bop);
+              if (uu == S::U - 1 && ks == S::KSTEPS - 1 && jb == JB - 1 && ib == WNB - 1)     // the trip's last
+                mfma_acc<true>(acc[ib][jb], abuf[slot_a][ib], bop);
+              else
+                mfma_acc<false>(acc[ib][jb], abuf[slot_a][ib], bop);
               // The last group has read the operand: the load PF steps ahead goes into the same registers.  (Asked for
               // before the matrix instructions it needed registers of its own, and the copies that rotate those into
               // place at the loop's end waited for every load in flight, once per trip.)
@@ -296,9 +304,6 @@ __device__ __forceinline__ void lm_head_rows_tile(const LmHeadArgs& a, unsigned 
         const unsigned tmp = cur_off; cur_off = nxt_off; nxt_off = wr_off; wr_off = tmp;
       }
     }
-    // the accumulators written by the last matrix instructions are read by vector instructions next; the
-    // compiler does not see an MFMA inside the asm statement, so the required wait states are spelled out
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
   }
 
   // ---- row reduction of the tile: the maximum over this lane's vocabulary ids and the four lane groups first, so that

@@ -310,19 +310,18 @@ __device__ __forceinline__ void lm_head_rows_tile(const LmHeadArgs& a, unsigned 
   // every exponential is taken relative to it and the rest are plain sums (one pairwise merge per exchange through the
   // LDS crossbar before: 126464 x 4096 packed, 256 positions 278 -> 270 us, 512: 498 -> 494); then over the waves
   const int n0 = tile * S::BN + wave * (WNB * 16) + 4 * q;     // this lane's ids: n0 + 16 ib + r
-  const bool past_v = tile * S::BN + S::BN > a.V;              // uniform: the last tile may run past V
+  const int left = a.V - n0;                                   // the last tile may run past V
 #pragma unroll
   for (int jb = 0; jb < JB; ++jb) {
+    // this row block's accumulators leave the accumulation registers here: copied out earlier, up to 33 registers of
+    // the 16-block tile went to scratch memory
+#pragma unroll
+    for (int ib = 0; ib < WNB; ++ib) asm volatile("" : "+a"(acc[ib][jb]));
     float v[WNB * 4];
 #pragma unroll
     for (int ib = 0; ib < WNB; ++ib)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v[ib * 4 + r] = acc[ib][jb][r];
-    if (past_v) {
-#pragma unroll
-      for (int i = 0; i < WNB * 4; ++i)
-        if (n0 + 16 * (i / 4) + i % 4 >= a.V) v[i] = -INFINITY;
-    }
+      for (int r = 0; r < 4; ++r) v[ib * 4 + r] = 16 * ib + r < left ? acc[ib][jb][r] : -INFINITY;
     float m = kNegBig;
 #pragma unroll
     for (int i = 0; i < WNB * 4; ++i) m = fmaxf(m, v[i]);

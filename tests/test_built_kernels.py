@@ -78,3 +78,15 @@ def test_projection_accumulators_are_read_after_the_wait(images):
             elif last is not None and re.search(r"\ba(\d+\b|\[)", s):
                 assert waited, f"{name}: {s} {i - last} instructions behind the last matrix instruction, no wait"
         assert loops == 4, name                          # one per chunk size
+
+
+def test_projection_rows_do_not_spill(images):
+    """lm_head_rows_kernel uses every register of a wave; a spill would cost each of its workgroups the stores."""
+    seen = 0
+    for path in images:
+        for entry in tool("llvm-readelf", "--notes", path).split("- .agpr_count")[1:]:
+            if "lm_head_rows_kernel" in re.search(r"\.name:\s+(\S+)", entry).group(1):
+                seen += 1
+                for key in ("private_segment_fixed_size", "vgpr_spill_count", "sgpr_spill_count"):
+                    assert int(re.search(r"\.%s:\s+(\d+)" % key, entry).group(1)) == 0, key
+    assert seen == 2

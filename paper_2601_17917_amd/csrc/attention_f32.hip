@@ -21,6 +21,7 @@
 // x 128, 64 query rows x 672 keys: 26 us (55 TFLOP/s, matrix pipe 40 % busy) against 276 us for one query row per wave
 // with fp32 FMAs out of LDS; B1, 4 heads x 64, 48 x 112: 7.2 against 17.5 us.
 #include "common.h"
+#include <cfloat>
 
 namespace sdllm {
 
@@ -150,9 +151,9 @@ __device__ __forceinline__ void f32_accumulate(const AttnF32Args& a, const f32x4
   mx = fmaxf(__uint_as_float(s16[0]), __uint_as_float(s16[1]));
   const auto s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
   mx = fmaxf(__uint_as_float(s32[0]), __uint_as_float(s32[1]));
-  const float m_new = fmaxf(m, mx);                // finite: a block holds at least one key
+  const float m_new = fmaxf(m, mx);                // not -inf, also where every score so far is: those weigh exp(-inf) = 0
   if (__builtin_amdgcn_ballot_w64(m_new != m) != 0) {      // uniform: some row's reference moves
-    const float corr = expf(m - m_new);            // first block: exp(-inf) = 0
+    const float corr = expf(m - m_new);            // first block: 0 (or 1, and nothing to scale)
     l *= corr;
 #pragma unroll
     for (int dg = 0; dg < NS / 4; ++dg)
@@ -160,16 +161,17 @@ __device__ __forceinline__ void f32_accumulate(const AttnF32Args& a, const f32x4
       for (int j = 0; j < 4; ++j) o[dg][j] *= corr;
     m = m_new;
   }
+  // key by key: the matrix instructions of one key cover the next one's exponential
   float p[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) p[i] = expf(sc[i] - m_new);
-  l += (p[0] + p[1]) + (p[2] + p[3]);              // this lane's keys; summed across the row's lanes at the end
+  for (int i = 0; i < 4; ++i) {
+    p[i] = expf(sc[i] - m_new);
 #pragma unroll
-  for (int dg = 0; dg < NS / 4; ++dg)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int dg = 0; dg < NS / 4; ++dg)
 #pragma unroll
       for (int j = 0; j < 4; ++j) o[dg][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[dg][i][j], p[i], o[dg][j], 0, 0, 0);
+  }
+  l += (p[0] + p[1]) + (p[2] + p[3]);              // this lane's keys; summed across the row's lanes at the end
 }
 
 template <int NS>
@@ -217,7 +219,8 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
   for (int dg = 0; dg < NS / 4; ++dg)
 #pragma unroll
     for (int j = 0; j < 4; ++j) o[dg][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, l = 0.f;
+  // the lowest finite reference, not -inf: scores may be -inf themselves (overflow, infinite operands), also all of a block
+  float m = -FLT_MAX, l = 0.f;
 
   // ---- key blocks wk, wk + nk, ...: a block's V travels during its scores, the next block's K during its P V
   for (int blk = wk; blk < a.key_blocks; blk += a.nk) {

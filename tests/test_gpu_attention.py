@@ -93,6 +93,25 @@ def test_attention_fp32_workgroup_shapes(gpu_lib, B, Hq, Hkv, D, P, K, S, keep, 
     assert np.abs(got - oracle(t, P)).max() <= TOL["fp32"]
 
 
+@pytest.mark.parametrize("D,P,K,first,nkeys", [
+    (64, 300, 20, 0, 16),           # the first key block: every score of one wave's first block is -inf
+    (64, 300, 20, 80, 16),          # ... of another wave
+    (128, 300, 20, 0, 128),         # ... of all eight waves
+    (256, 100, 5, 48, 16),          # four waves
+    (64, 16, 9, 0, 16),             # two key blocks
+])
+def test_attention_fp32_scores_that_overflow(gpu_lib, D, P, K, first, nkeys):
+    """Finite inputs whose scores lie below the fp32 range for some keys: those keys have weight zero, the others
+    share the row."""
+    t = wl.make_custom_attention_inputs("fp32", 1, 2, 1, D, P, P, K, 1, (), seed=D + first)
+    for name in ("q_block", "k_cache", "k_block"):
+        t[name][..., 0] = 0.0
+    t["q_block"][..., 0] = 1e20
+    t["k_cache"][:, :, first:first + nkeys, 0] = -1e20
+    got = run_gpu(gpu_lib, t, P)
+    assert np.abs(got - oracle(t, P)).max() <= TOL["fp32"]
+
+
 @pytest.mark.parametrize("kv_splits", [0, 1, 2, 3])
 def test_attention_small_bf16(gpu_lib, kv_splits):
     w = wl.WORKLOADS["small_bf16"]             # GQA 4/2, P=107, K=32, s=33: ragged key and query tiles

@@ -95,8 +95,8 @@ __device__ __forceinline__ void f32_rows(const AttnF32Args& a, f32_gptr tc, f32_
   }
 }
 
-// The loops below run over all NS slices whatever D is (no branches: the loads of a block travel together and the
-// wait counts stay exact); slices past D re-read the row's last elements, meet zeros of Q and are never stored.
+// The loads below run over all NS slices whatever D is (no branches: the loads of a block travel together and the
+// wait counts stay exact); past D they re-read the row's last elements, which no product takes and no store writes.
 // K operands: lane (l16, G) takes d = 16 s + 4 G .. + 3 of key l16
 template <int NS>
 __device__ __forceinline__ void f32_load_k(const AttnF32Args& a, int l16, int G, f32_gptr tc, f32_gptr tb, f32_gptr ts, int blk,
@@ -127,14 +127,24 @@ __device__ __forceinline__ void f32_load_v(const AttnF32Args& a, int l16, int G,
     for (int i = 0; i < 4; ++i) v[dg][i] = f32_load4(vp[i] + min(64 * dg + 4 * l16, a.D - 4));
 }
 
-// S^T of one key block, times the scale; keys past the end at -inf
-template <int NS>
+// S^T of one key block, times the scale.  RAGGED: the head is narrower than its NS slices; slices past D are left out,
+// and in the one that D ends in K becomes zero like Q (the re-read elements may be infinite, and zero times those is NaN).  Keys past the end get -inf.
+template <int NS, bool RAGGED>
 __device__ __forceinline__ f32x4 f32_scores(const AttnF32Args& a, int G, int blk, const f32x4 (&k)[NS], const f32x4 (&q)[NS]) {
   f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-  for (int s = 0; s < NS; ++s)
+  for (int s = 0; s < NS; ++s) {
+    constexpr int kWhole = NS == 4 ? 0 : NS / 2;   // slices that every width served by this NS fills
+    if (RAGGED && s >= kWhole && 16 * s >= a.D) break;       // uniform
+    f32x4 ks = k[s];
+    if (RAGGED && s >= kWhole && 16 * s + 16 > a.D) {        // uniform
+      // (holds the branch: turned into selects in every slice, a 252-wide layer, 64 rows x 736 keys, took 43.8 us, not 41.2)
+      asm volatile("");
+      if (16 * s + 4 * G >= a.D) ks = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[s][j], q[s][j], acc[j & 1], 0, 0, 0);
+    for (int j = 0; j < 4; ++j) acc[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(ks[j], q[s][j], acc[j & 1], 0, 0, 0);
+  }
   f32x4 sc = (acc[0] + acc[1]) * a.scale;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -174,7 +184,7 @@ __device__ __forceinline__ void f32_accumulate(const AttnF32Args& a, const f32x4
   l += (p[0] + p[1]) + (p[2] + p[3]);              // this lane's keys; summed across the row's lanes at the end
 }
 
-template <int NS>
+template <int NS, bool RAGGED>
 __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) void attention_f32_kernel(AttnF32Args a) {
   extern __shared__ __attribute__((aligned(16))) float f32_lds[];
   const int lane = threadIdx.x & 63, l16 = lane & 15, G = lane >> 4;
@@ -209,7 +219,7 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
   f32x4 q[NS];
 #pragma unroll
   for (int s = 0; s < NS; ++s) q[s] = f32_load4(qp + min(16 * s + 4 * G, D - 4));
-  if (D < 16 * NS) {                               // uniform (the selects wait for the rows)
+  if constexpr (RAGGED) {
 #pragma unroll
     for (int s = 0; s < NS; ++s)
       if (16 * s + 4 * G >= D) q[s] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -226,7 +236,7 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
   for (int blk = wk; blk < a.key_blocks; blk += a.nk) {
     f32_load_v<NS>(a, l16, G, vc, vb, vs, blk, ka, v);
     ka = f32_ahead(a, blk + a.nk);
-    const f32x4 sc = f32_scores<NS>(a, G, blk, k, q);
+    const f32x4 sc = f32_scores<NS, RAGGED>(a, G, blk, k, q);
     f32_load_k<NS>(a, l16, G, kc, kb, ks, min(blk + a.nk, a.key_blocks - 1), ka, k);     // (past the end: never used)
     f32_accumulate<NS>(a, sc, v, o, m, l);
   }
@@ -309,26 +319,30 @@ void attention_f32_plan(const sdllm_attn_params& p, sdllm_attn_plan* plan) {
 
 template <int NS> constexpr size_t f32_lds_bytes(int waves) { return (size_t)waves * (NS * 1024 + 16 * sizeof(float2)); }
 
-template <int NS>
+template <int NS, bool RAGGED>
 static hipError_t f32_opt_in() {
   static LdsOptIn st;
-  return ensure_lds_opt_in(reinterpret_cast<const void*>(&attention_f32_kernel<NS>), f32_lds_bytes<NS>(f32_max_waves<NS>()), st);
+  return ensure_lds_opt_in(reinterpret_cast<const void*>(&attention_f32_kernel<NS, RAGGED>),
+                           f32_lds_bytes<NS>(f32_max_waves<NS>()), st);
 }
 
 hipError_t prepare_attention_f32() {
-  hipError_t e = f32_opt_in<4>();
-  if (e == hipSuccess) e = f32_opt_in<8>();
-  if (e == hipSuccess) e = f32_opt_in<16>();
+  hipError_t e = f32_opt_in<4, false>();
+  if (e == hipSuccess) e = f32_opt_in<4, true>();
+  if (e == hipSuccess) e = f32_opt_in<8, false>();
+  if (e == hipSuccess) e = f32_opt_in<8, true>();
+  if (e == hipSuccess) e = f32_opt_in<16, false>();
+  if (e == hipSuccess) e = f32_opt_in<16, true>();
   return e;
 }
 
-template <int NS>
+template <int NS, bool RAGGED>
 static hipError_t f32_launch(const AttnF32Args& a, const F32Plan& pl, hipStream_t stream) {
-  const hipError_t e = f32_opt_in<NS>();
+  const hipError_t e = f32_opt_in<NS, RAGGED>();
   if (e != hipSuccess) return e;
   const int waves = pl.nr * pl.nk;
-  hipLaunchKernelGGL(attention_f32_kernel<NS>, dim3(pl.workgroups), dim3(64 * waves), pl.nk > 1 ? f32_lds_bytes<NS>(waves) : 0,
-                     stream, a);
+  hipLaunchKernelGGL((attention_f32_kernel<NS, RAGGED>), dim3(pl.workgroups), dim3(64 * waves),
+                     pl.nk > 1 ? f32_lds_bytes<NS>(waves) : 0, stream, a);
   return hipGetLastError();
 }
 
@@ -352,9 +366,14 @@ hipError_t launch_attention_f32(const sdllm_attn_params& p,
   a.n_groups = p.B * p.Hkv; a.q_tiles = pl.q_tiles; a.key_blocks = (a.Nkv + kF32Keys - 1) / kF32Keys;
   a.nr = pl.nr; a.nk = pl.nk; a.xcd_map = pl.xcd_map;
   a.scale = p.scale > 0.f ? p.scale : 1.0f / sqrtf((float)p.D);
-  if (p.D <= 64) return f32_launch<4>(a, pl, stream);
-  if (p.D <= 128) return f32_launch<8>(a, pl, stream);
-  return f32_launch<16>(a, pl, stream);
+  switch (p.D) {
+    case 64: return f32_launch<4, false>(a, pl, stream);
+    case 128: return f32_launch<8, false>(a, pl, stream);
+    case 256: return f32_launch<16, false>(a, pl, stream);
+  }
+  if (p.D < 64) return f32_launch<4, true>(a, pl, stream);
+  if (p.D < 128) return f32_launch<8, true>(a, pl, stream);
+  return f32_launch<16, true>(a, pl, stream);
 }
 
 }  // namespace sdllm

@@ -112,6 +112,20 @@ def test_attention_fp32_scores_that_overflow(gpu_lib, D, P, K, first, nkeys):
     assert np.abs(got - oracle(t, P)).max() <= TOL["fp32"]
 
 
+@pytest.mark.parametrize("D", [4, 20, 52, 80, 124, 132, 252])
+def test_attention_fp32_infinite_last_element_of_k(gpu_lib, D):
+    """A key whose last element makes its scores -inf has weight zero, also where the head does not fill the 16-element
+    slices of the kernel."""
+    t = wl.make_custom_attention_inputs("fp32", 1, 2, 1, D, 37, 40, 5, 9, (2, 3, 8), seed=D)
+    for name in ("q_block", "q_suffix"):
+        t[name][..., D - 1] = np.abs(t[name][..., D - 1]) + 0.1
+    t["k_cache"][:, :, 3, D - 1] = -np.inf
+    t["k_block"][:, :, 4, D - 1] = -np.inf
+    t["k_suffix"][:, :, 8, D - 1] = -np.inf
+    got = run_gpu(gpu_lib, t, 37)
+    assert np.abs(got - oracle(t, 37)).max() <= TOL["fp32"]
+
+
 @pytest.mark.parametrize("kv_splits", [0, 1, 2, 3])
 def test_attention_small_bf16(gpu_lib, kv_splits):
     w = wl.WORKLOADS["small_bf16"]             # GQA 4/2, P=107, K=32, s=33: ragged key and query tiles

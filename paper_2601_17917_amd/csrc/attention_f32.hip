@@ -22,6 +22,7 @@
 // with fp32 FMAs out of LDS; B1, 4 heads x 64, 48 x 112: 7.2 against 17.5 us.
 #include "common.h"
 #include <cfloat>
+#include <type_traits>
 
 namespace sdllm {
 
@@ -128,8 +129,9 @@ __device__ __forceinline__ void f32_load_v(const AttnF32Args& a, int l16, int G,
 }
 
 // S^T of one key block, times the scale.  RAGGED: the head is narrower than its NS slices; slices past D are left out,
-// and in the one that D ends in K becomes zero like Q (the re-read elements may be infinite, and zero times those is NaN).  Keys past the end get -inf.
-template <int NS, bool RAGGED>
+// and in the one that D ends in K becomes zero like Q (the re-read elements may be infinite, and zero times those is NaN).
+// PARTIAL: the sequence's last keys, fewer than a block; those past the end get -inf.
+template <int NS, bool RAGGED, bool PARTIAL>
 __device__ __forceinline__ f32x4 f32_scores(const AttnF32Args& a, int G, int blk, const f32x4 (&k)[NS], const f32x4 (&q)[NS]) {
   f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
@@ -146,15 +148,17 @@ __device__ __forceinline__ f32x4 f32_scores(const AttnF32Args& a, int G, int blk
     for (int j = 0; j < 4; ++j) acc[j & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(ks[j], q[s][j], acc[j & 1], 0, 0, 0);
   }
   f32x4 sc = (acc[0] + acc[1]) * a.scale;
+  if constexpr (PARTIAL) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (blk * kF32Keys + 4 * G + i >= a.Nkv) sc[i] = -INFINITY;
+    for (int i = 0; i < 4; ++i)
+      if (blk * kF32Keys + 4 * G + i >= a.Nkv) sc[i] = -INFINITY;
+  }
   return sc;
 }
 
 // Online softmax step and O^T += V^T P^T
-template <int NS>
-__device__ __forceinline__ void f32_accumulate(const AttnF32Args& a, const f32x4& sc, const f32x4 (&v)[NS / 4][4],
+template <int NS, bool PARTIAL>
+__device__ __forceinline__ void f32_accumulate(const AttnF32Args& a, int G, int blk, const f32x4& sc, f32x4 (&v)[NS / 4][4],
                                                f32x4 (&o)[NS / 4][4], float& m, float& l) {
   float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
   const auto s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
@@ -170,6 +174,13 @@ __device__ __forceinline__ void f32_accumulate(const AttnF32Args& a, const f32x4
 #pragma unroll
       for (int j = 0; j < 4; ++j) o[dg][j] *= corr;
     m = m_new;
+  }
+  if constexpr (PARTIAL) {                         // zeros past the end: the re-read last row may be infinite, p is 0
+#pragma unroll
+    for (int dg = 0; dg < NS / 4; ++dg)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (blk * kF32Keys + 4 * G + i >= a.Nkv) v[dg][i] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   // key by key: the matrix instructions of one key cover the next one's exponential
   float p[4];
@@ -233,13 +244,17 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
   float m = -FLT_MAX, l = 0.f;
 
   // ---- key blocks wk, wk + nk, ...: a block's V travels during its scores, the next block's K during its P V
-  for (int blk = wk; blk < a.key_blocks; blk += a.nk) {
+  auto block = [&](int blk, auto partial) {
     f32_load_v<NS>(a, l16, G, vc, vb, vs, blk, ka, v);
     ka = f32_ahead(a, blk + a.nk);
-    const f32x4 sc = f32_scores<NS, RAGGED>(a, G, blk, k, q);
+    const f32x4 sc = f32_scores<NS, RAGGED, partial.value>(a, G, blk, k, q);
     f32_load_k<NS>(a, l16, G, kc, kb, ks, min(blk + a.nk, a.key_blocks - 1), ka, k);     // (past the end: never used)
-    f32_accumulate<NS>(a, sc, v, o, m, l);
-  }
+    f32_accumulate<NS, partial.value>(a, G, blk, sc, v, o, m, l);
+  };
+  const int full = a.Nkv / kF32Keys;
+  int blk = wk;
+  for (; blk < full; blk += a.nk) block(blk, std::false_type{});
+  if (blk < a.key_blocks) block(blk, std::true_type{});      // the sequence's last keys, not a whole block
   l += __shfl_xor(l, 16);
   l += __shfl_xor(l, 32);
 

@@ -126,6 +126,19 @@ def test_attention_fp32_infinite_last_element_of_k(gpu_lib, D):
     assert np.abs(got - oracle(t, 37)).max() <= TOL["fp32"]
 
 
+@pytest.mark.parametrize("D,P,K", [(64, 37, 4), (80, 11, 4), (128, 300, 5), (256, 61, 2), (4, 0, 1)])
+def test_attention_fp32_infinite_last_row_of_v(gpu_lib, D, P, K):
+    """The last key's V row is infinite in one column and the number of keys is no multiple of the key block: that
+    column of the output is infinite, the others are what they are without it."""
+    assert (P + K) % 16 != 0
+    t = wl.make_custom_attention_inputs("fp32", 1, 2, 1, D, P, max(P, 1), K, 1, (), seed=D)
+    t["v_block"][:, :, K - 1, 1] = np.inf
+    got, want = run_gpu(gpu_lib, t, P), oracle(t, P)
+    assert np.isposinf(want[..., 1]).all() and np.isposinf(got[..., 1]).all()
+    keep = np.arange(D) != 1
+    assert np.abs(got[..., keep] - want[..., keep]).max() <= TOL["fp32"]
+
+
 @pytest.mark.parametrize("kv_splits", [0, 1, 2, 3])
 def test_attention_small_bf16(gpu_lib, kv_splits):
     w = wl.WORKLOADS["small_bf16"]             # GQA 4/2, P=107, K=32, s=33: ragged key and query tiles

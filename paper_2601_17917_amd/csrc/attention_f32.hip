@@ -21,6 +21,7 @@
 // x 128, 64 query rows x 672 keys: 26 us (55 TFLOP/s, matrix pipe 40 % busy) against 276 us for one query row per wave
 // with fp32 FMAs out of LDS; B1, 4 heads x 64, 48 x 112: 7.2 against 17.5 us.
 #include "common.h"
+#include <algorithm>
 #include <cfloat>
 #include <type_traits>
 
@@ -44,6 +45,9 @@ struct AttnF32Args {
 
 constexpr int kF32Rows = 16;      // query rows per wave
 constexpr int kF32Keys = 16;      // keys per block
+// Workgroups in a row of the grid: a launch takes fewer than 2^32 work-items in each dimension, which 2^23 workgroups of
+// 512 would reach.  A multiple of the chip's parts, so that the workgroup number mod 8 is the part in every row.
+constexpr unsigned kF32GridX = 1u << 22;
 
 // most waves of a workgroup: 8 (two per SIMD); 4 for 256-wide heads, whose operands and accumulators need the registers
 template <int NS> constexpr int f32_max_waves() { return NS <= 8 ? 8 : 4; }
@@ -202,14 +206,17 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = wave % a.nr, wk = wave / a.nr;
   // ---- which piece of work: with xcd_map the row tiles of a group sit on one XCD (its L2 holds the group's K/V)
-  int grp, qt;
+  const unsigned wg = blockIdx.y * kF32GridX + blockIdx.x, q_tiles = a.q_tiles;
+  unsigned ugrp;
+  int qt;
   if (a.xcd_map) {
-    const int xcd = blockIdx.x % kNumXCDs, slot = blockIdx.x / kNumXCDs;
-    grp = (slot / a.q_tiles) * kNumXCDs + xcd; qt = slot % a.q_tiles;
+    const unsigned xcd = wg % kNumXCDs, slot = wg / kNumXCDs;
+    ugrp = (slot / q_tiles) * kNumXCDs + xcd; qt = slot % q_tiles;
   } else {
-    grp = blockIdx.x / a.q_tiles; qt = blockIdx.x % a.q_tiles;
+    ugrp = wg / q_tiles; qt = wg % q_tiles;
   }
-  if (grp >= a.n_groups) return;
+  if (ugrp >= (unsigned)a.n_groups) return;
+  const int grp = ugrp;
   const int b = grp / a.Hkv, kvh = grp - b * a.Hkv, D = a.D;
   const long long bh = grp;
   const f32_gptr kc = (f32_gptr)a.k_cache + bh * a.cap * D, vc = (f32_gptr)a.v_cache + bh * a.cap * D;
@@ -306,7 +313,7 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
 // Waves of a workgroup.  T = 16-row blocks of the call, aim = 8 waves per CU (two per SIMD).  Up to 256 blocks a
 // workgroup holds one block and splits the keys eight ways; with more blocks than CUs it takes 2, 4, 8 of them (they share
 // K/V in the L1) and splits the keys correspondingly less, as long as the last tile of a group is not mostly empty.
-struct F32Plan { int nr, nk, q_tiles, workgroups, xcd_map; };
+struct F32Plan { int nr, nk, q_tiles, xcd_map; long long workgroups; };
 static F32Plan plan_attention_f32(const sdllm_attn_params& p) {
   const int max_waves = p.D <= 128 ? f32_max_waves<8>() : f32_max_waves<16>();
   const long long Rtot = (long long)(p.Hq / p.Hkv) * (p.K + p.n_keep);
@@ -321,13 +328,13 @@ static F32Plan plan_attention_f32(const sdllm_attn_params& p) {
   pl.q_tiles = (int)((tiles + pl.nr - 1) / pl.nr);
   const long long padded = (groups + kNumXCDs - 1) / kNumXCDs * kNumXCDs;
   pl.xcd_map = padded * 4 <= groups * 5;
-  pl.workgroups = (int)((pl.xcd_map ? padded : groups) * pl.q_tiles);
+  pl.workgroups = (pl.xcd_map ? padded : groups) * pl.q_tiles;
   return pl;
 }
 
 void attention_f32_plan(const sdllm_attn_params& p, sdllm_attn_plan* plan) {
   const F32Plan pl = plan_attention_f32(p);
-  plan->kv_splits = 1; plan->rows_per_workgroup = kF32Rows * pl.nr; plan->workgroups = pl.workgroups;
+  plan->kv_splits = 1; plan->rows_per_workgroup = kF32Rows * pl.nr; plan->workgroups = (int32_t)std::min(pl.workgroups, 0x7fffffffLL);
   plan->key_tiles_per_split = (p.prefix_len + p.K + p.n_keep + kF32Keys - 1) / kF32Keys;
   plan->workgroup_shape = 0; plan->ring_stages = 2;
 }
@@ -356,8 +363,8 @@ static hipError_t f32_launch(const AttnF32Args& a, const F32Plan& pl, hipStream_
   const hipError_t e = f32_opt_in<NS, RAGGED>();
   if (e != hipSuccess) return e;
   const int waves = pl.nr * pl.nk;
-  hipLaunchKernelGGL((attention_f32_kernel<NS, RAGGED>), dim3(pl.workgroups), dim3(64 * waves),
-                     pl.nk > 1 ? f32_lds_bytes<NS>(waves) : 0, stream, a);
+  const dim3 grid((unsigned)std::min(pl.workgroups, (long long)kF32GridX), (unsigned)((pl.workgroups + kF32GridX - 1) / kF32GridX));
+  hipLaunchKernelGGL((attention_f32_kernel<NS, RAGGED>), grid, dim3(64 * waves), pl.nk > 1 ? f32_lds_bytes<NS>(waves) : 0, stream, a);
   return hipGetLastError();
 }
 

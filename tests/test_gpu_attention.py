@@ -139,6 +139,16 @@ def test_attention_fp32_infinite_last_row_of_v(gpu_lib, D, P, K):
     assert np.abs(got[..., keep] - want[..., keep]).max() <= TOL["fp32"]
 
 
+def test_attention_fp32_more_groups_than_one_grid_row(gpu_lib):
+    """1025 x 65535 heads of one query and one key, whose output is the key's V row: 2^32 work-items and more."""
+    B, H, D = 1025, 65535, 4
+    q, k = (torch.ones((B, H, 1, D), device="cuda") for _ in range(2))
+    v = torch.randn((B, H, 1, D), device="cuda")
+    assert gpu_lib.plan_attention(gpu_lib.attn_params(gpu_lib.FP32, B, H, H, D, 0, 0, 1, 0, 0)).workgroups * 64 >= 1 << 32
+    out = gpu_lib.block_attention(q, None, None, None, k, v, None, None, None, 0)
+    assert torch.equal(out, v)
+
+
 @pytest.mark.parametrize("kv_splits", [0, 1, 2, 3])
 def test_attention_small_bf16(gpu_lib, kv_splits):
     w = wl.WORKLOADS["small_bf16"]             # GQA 4/2, P=107, K=32, s=33: ragged key and query tiles

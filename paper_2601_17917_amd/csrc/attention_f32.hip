@@ -310,9 +310,15 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
   }
 }
 
-// Waves of a workgroup.  T = 16-row blocks of the call, aim = 8 waves per CU (two per SIMD).  Up to 256 blocks a
-// workgroup holds one block and splits the keys eight ways; with more blocks than CUs it takes 2, 4, 8 of them (they share
-// K/V in the L1) and splits the keys correspondingly less, as long as the last tile of a group is not mostly empty.
+// Waves of a workgroup: NR row blocks x NK key shares.  The aim is 8 waves per CU (two per SIMD).
+//   NR  1 unless the call has 16-row blocks for two (four, eight) per CU; then a workgroup holds as many, which share K/V in
+//       the L1, as long as the last tile of a group is not mostly empty.
+//   NK  what NR leaves of the workgroup's waves, but no more than there are key blocks.  Where the call has 8 waves per CU
+//       with half as many shares, a share holds at least 4 key blocks: the merge through LDS costs as much as several of
+//       them.  Measured with / without that: 32768 groups of one row, 4 wide, 65 keys 95 / 320 us (one query row per
+//       wave with FMAs: 174), 2048 groups of one row, 16 wide, 65 keys 9.4 / 23.0 (18.4), 8192 groups of one row, 128
+//       wide, 65 keys 99 / 244 (304).  With 8 blocks as the limit, 3200 groups of 10 rows, 64 wide, 710 keys took 205
+//       us, not 202; without one, 2048 groups of one row, 64 wide, 1025 keys 184, not 177.
 struct F32Plan { int nr, nk, q_tiles, xcd_map; long long workgroups; };
 static F32Plan plan_attention_f32(const sdllm_attn_params& p) {
   const int max_waves = p.D <= 128 ? f32_max_waves<8>() : f32_max_waves<16>();
@@ -326,6 +332,7 @@ static F32Plan plan_attention_f32(const sdllm_attn_params& p) {
   pl.nk = max_waves / pl.nr;
   while (pl.nk > 1 && pl.nk / 2 >= blocks) pl.nk >>= 1;
   pl.q_tiles = (int)((tiles + pl.nr - 1) / pl.nr);
+  while (pl.nk > 1 && blocks < 4 * pl.nk && groups * pl.q_tiles * pl.nr * (pl.nk / 2) >= 8LL * kNumCUs) pl.nk >>= 1;
   const long long padded = (groups + kNumXCDs - 1) / kNumXCDs * kNumXCDs;
   pl.xcd_map = padded * 4 <= groups * 5;
   pl.workgroups = (pl.xcd_map ? padded : groups) * pl.q_tiles;

@@ -79,6 +79,11 @@ def test_attention_fp32_shapes(gpu_lib, B, Hq, Hkv, D, P, cap, K, S, keep):
     (1, 2, 1, 128, 112, 16, 64, tuple(range(16, 48)), 1),         # suffix blocks on consecutive rows
     (1, 2, 1, 132, 50, 15, 33, tuple(range(0, 33, 2)), 1),        # ... on scattered rows; D > 128: four waves
     (9, 1, 1, 64, 33, 5, 0, (), 1),                               # group count that does not fit the 8 chip parts
+    # enough groups for the chip: the keys in one, two and four shares of at least four blocks, or one of fewer
+    (64, 32, 32, 16, 64, 1, 0, (), 1),
+    (32, 32, 32, 8, 90, 1, 7, (2, 6), 1),
+    (32, 16, 16, 64, 235, 3, 0, (), 1),
+    (32, 64, 32, 132, 20, 2, 0, (), 1),
     # two, four and eight row blocks per workgroup (from 512 row blocks on), the last tile of a group ragged
     (16, 16, 16, 32, 10, 30, 0, (), 2),
     (16, 64, 16, 64, 20, 16, 0, (), 4),

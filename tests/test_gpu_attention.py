@@ -84,7 +84,7 @@ def test_attention_fp32_shapes(gpu_lib, B, Hq, Hkv, D, P, cap, K, S, keep):
     (32, 32, 32, 8, 90, 1, 7, (2, 6), 1),
     (32, 16, 16, 64, 235, 3, 0, (), 1),
     (32, 64, 32, 132, 20, 2, 0, (), 1),
-    # two, four and eight row blocks per workgroup (from 512 row blocks on), the last tile of a group ragged
+    # two, four and eight row blocks per workgroup (from 512 row blocks on), one workgroup per group
     (16, 16, 16, 32, 10, 30, 0, (), 2),
     (16, 64, 16, 64, 20, 16, 0, (), 4),
     (16, 64, 16, 16, 7, 31, 1, (0,), 8),
@@ -94,6 +94,28 @@ def test_attention_fp32_workgroup_shapes(gpu_lib, B, Hq, Hkv, D, P, K, S, keep, 
     p = gpu_lib.attn_params(gpu_lib.FP32, B, Hq, Hkv, D, P, P + 3, K, S, len(keep))
     assert gpu_lib.plan_attention(p).rows_per_workgroup == 16 * nr
     t = wl.make_custom_attention_inputs("fp32", B, Hq, Hkv, D, P, P + 3, K, max(S, 1), keep, seed=D + P)
+    got = run_gpu(gpu_lib, t, P)
+    assert np.abs(got - oracle(t, P)).max() <= TOL["fp32"]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,P,K,S,keep,nr,workgroups", [
+    # several workgroups per group and a last one whose waves do not all have rows: 15 row blocks as 8 x 2, 4 x 4, 2 x 8
+    (8, 20, 5, 16, 20, 57, 9, (0, 8), 2, 320),
+    (16, 20, 5, 16, 20, 57, 9, (0, 8), 4, 320),
+    (28, 20, 5, 16, 20, 57, 9, (0, 8), 8, 288),                   # 140 groups: padded to 144 for the 8 chip parts
+    (8, 20, 5, 132, 20, 57, 9, (0, 8), 2, 320),
+    # 25 groups, which do not fit the 8 chip parts: 21 row blocks as 11 x 2, 43 as 11 x 4, 83 as 11 x 8
+    (25, 8, 1, 16, 20, 40, 9, (3, 4), 2, 275),
+    (25, 17, 1, 16, 9, 40, 0, (), 4, 275),
+    (25, 33, 1, 16, 9, 40, 0, (), 8, 275),
+])
+def test_attention_fp32_several_row_tiles(gpu_lib, B, Hq, Hkv, D, P, K, S, keep, nr, workgroups):
+    p = gpu_lib.attn_params(gpu_lib.FP32, B, Hq, Hkv, D, P, P, K, S, len(keep))
+    plan = gpu_lib.plan_attention(p)
+    assert (plan.rows_per_workgroup, plan.workgroups) == (16 * nr, workgroups)
+    rows = Hq // Hkv * (K + len(keep))
+    assert -(-rows // 16) % nr != 0                               # row blocks of a group that fill no whole workgroup
+    t = wl.make_custom_attention_inputs("fp32", B, Hq, Hkv, D, P, P, K, max(S, 1), keep, seed=B + D)
     got = run_gpu(gpu_lib, t, P)
     assert np.abs(got - oracle(t, P)).max() <= TOL["fp32"]
 

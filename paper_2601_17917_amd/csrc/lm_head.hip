@@ -17,7 +17,7 @@
 //     lane exchanges, then across the four waves through LDS.
 //   * Row chunks of one vocabulary tile get workgroup ids that are equal mod 8 and adjacent in
 //     dispatch order: same XCD, same L2, so W comes from HBM once.
-//   * Shapes: with 256 rows per chunk (more than 128 masked positions) lm_head_rows_kernel is bound by
+//   * Shapes: more than 128 masked positions go to lm_head_rows_kernel in chunks of 160 to 256 rows.  It is bound by
 //     the matrix pipe (one wave per SIMD, accumulators in the accumulation registers, B operands through
 //     a register ring fed across chunk boundaries).  Calls with at most 128 masked positions are a read
 //     of W and take the stream kernels further down, which turn the roles around: the hidden operands
@@ -82,6 +82,11 @@ __device__ __forceinline__ int lm_masked_count(const LmHeadArgs& a, int* wsum) {
 }
 
 
+// lm_head_rows_kernel: BM rows of positions per chunk at most, WNB 16-row blocks of W per wave, PF k-steps of W in flight
+// per wave.  It is bound by the matrix pipe with one wave per SIMD.  Its accumulators (256 registers for a full chunk) sit
+// in the accumulation half of the register file by construction (left to the register allocator they were shuffled
+// between the halves inside the loop, or spilled), and its B operands run through a register ring DB deep that is fed
+// across chunk boundaries, which takes a third LDS stage (a chunk is complete one barrier before it is first read).
 template <int BM, int WNB, int PF_>
 struct LmShape {
   static constexpr int BN = kLmWaves * WNB * 16;            // vocabulary rows per workgroup
@@ -89,25 +94,16 @@ struct LmShape {
   static constexpr int KSTEPS = KC / 32;                    // MFMA k-steps per stage
   static constexpr int PIECES = KC / 8;                     // 16-byte pieces per LDS row
   static constexpr int PF = PF_;                            // k-steps of W in flight per wave
-  static constexpr int U = PF > KSTEPS ? PF / KSTEPS : 1;   // chunks per unrolled loop body (static ring slots)
+  static constexpr int U = PF / KSTEPS;                     // chunks per unrolled loop body (static ring slots)
   static constexpr int ROWS_PER_PASS = kLmThreads / PIECES; // rows one staging pass of the workgroup covers
-  static constexpr int MIN_WAVES = BM <= 64 ? 2 : 1;        // waves per SIMD the register budget must allow
-  // The wide shapes are bound by the matrix pipe with one wave per SIMD.  Their 128 / 256 accumulator
-  // registers sit in the accumulation half of the register file by construction (left to the register
-  // allocator they were shuffled between the halves inside the loop, or spilled), and their B operands
-  // run through a register ring DB deep that is fed across chunk boundaries, which takes a third LDS
-  // stage (a chunk is complete one barrier before it is first read).
-  static constexpr bool WIDE = BM >= 128;
-  static constexpr int NST = WIDE ? 3 : 2;
+  static constexpr int NST = 3;
   static constexpr int DB = 8;
-  static constexpr int HDEPTH = KSTEPS >= 4 ? 1 : 4 / KSTEPS;   // chunks a hidden chunk waits in registers (wide)
-  static_assert((PIECES == 8 || PIECES % 16 == 0) && kLmThreads % PIECES == 0, "shape");
-  static_assert((KSTEPS * U) % PF == 0 && (U == 1 || U % 2 == 0) && (!WIDE || U % HDEPTH == 0), "ring");
+  static constexpr int HDEPTH = 4 / KSTEPS;                 // chunks a hidden chunk waits in registers
+  static_assert(PIECES == 8 && kLmThreads % PIECES == 0, "shape (swz)");
+  static_assert(KSTEPS > 1 && PF > KSTEPS && (KSTEPS * U) % PF == 0 && U % 2 == 0 && U % HDEPTH == 0, "ring");
   // LDS rows are unpadded; piece p of row r sits at slot swz(r, p), chosen so that the 16 lanes of a
   // B-operand read (rows r..r+15, same piece) fall into 16 different 16-byte bank groups
-  __device__ static __forceinline__ int swz(int r, int p) {
-    return PIECES == 8 ? (p ^ ((r >> 1) & 7)) : (p ^ (r & 15));
-  }
+  __device__ static __forceinline__ int swz(int r, int p) { return p ^ ((r >> 1) & 7); }
 };
 
 template <bool NT = false>
@@ -211,98 +207,94 @@ __device__ __forceinline__ void lm_head_rows_tile(const LmHeadArgs& a, unsigned 
     }
   };
   stage_now(0, stage);
-  static_assert(S::WIDE, "only the 256-row shape is built: fewer positions take the stream kernels");
   stage_now(1, stage + kLmStageBytes);
   __syncthreads();
 
   const int NCHU = (NCH + S::U - 1) / S::U * S::U;      // chunks past NCH see zeros
-  if constexpr (S::WIDE) {
-    // ---- main loop, wide shapes: three LDS stages (read c, already complete c + 1, being written c + 2)
-    constexpr int CH = S::KSTEPS * JB;                  // B operands per chunk
-    static_assert(S::U * CH % S::DB == 0 && S::DB <= CH, "B ring");
-    static_assert(S::KSTEPS > 1, "staging loads and stores in different k-steps");
-    unsigned pv[S::KSTEPS];                             // per-lane part of a B-operand address, by k-step
+  // ---- main loop: three LDS stages (read c, already complete c + 1, being written c + 2)
+  constexpr int CH = S::KSTEPS * JB;                  // B operands per chunk
+  static_assert(S::U * CH % S::DB == 0 && S::DB <= CH, "B ring");
+  unsigned pv[S::KSTEPS];                             // per-lane part of a B-operand address, by k-step
 #pragma unroll
-    for (int ks = 0; ks < S::KSTEPS; ++ks) pv[ks] = boff + (unsigned)(S::swz(l16, 4 * ks + q) << 4);
-    auto read_b = [&](unsigned st_off, int ks, int jb) {
-      return *reinterpret_cast<const bf16x8*>(stage + st_off + pv[ks] + jb * 16 * S::KC * 2);
-    };
-    unsigned cur_off = 0, nxt_off = kLmStageBytes, wr_off = 2 * kLmStageBytes;    // uniform
-    bf16x8 bq[S::DB];
+  for (int ks = 0; ks < S::KSTEPS; ++ks) pv[ks] = boff + (unsigned)(S::swz(l16, 4 * ks + q) << 4);
+  auto read_b = [&](unsigned st_off, int ks, int jb) {
+    return *reinterpret_cast<const bf16x8*>(stage + st_off + pv[ks] + jb * 16 * S::KC * 2);
+  };
+  unsigned cur_off = 0, nxt_off = kLmStageBytes, wr_off = 2 * kLmStageBytes;    // uniform
+  bf16x8 bq[S::DB];
 #pragma unroll
-    for (int d = 0; d < S::DB; ++d) bq[d] = read_b(cur_off, d / JB, d % JB);
-    // Loads return in issue order, so waiting for a young load also waits for every older one: a hidden
-    // chunk that is consumed at the end of the chunk it was asked for in would drain the W ring down to
-    // the loads of that chunk, however far ahead the ring runs.  The hidden chunks therefore travel HD
-    // chunks ahead in registers, so that nothing younger than about PF k-steps is ever waited for.
-    constexpr int HD = S::HDEPTH;                       // chunks a hidden chunk waits in registers
-    u32x4 hreg[HD][NPASS];
-    auto load_hidden = [&](int c, u32x4 (&dst)[NPASS]) {      // chunk at walk position c (zeros past the end)
-      const unsigned k = (unsigned)(chunk_at(c < NCH ? c : 0) * S::KC) + 8u * pc;
-      const unsigned kc = min(k, klast);
+  for (int d = 0; d < S::DB; ++d) bq[d] = read_b(cur_off, d / JB, d % JB);
+  // Loads return in issue order, so waiting for a young load also waits for every older one: a hidden
+  // chunk that is consumed at the end of the chunk it was asked for in would drain the W ring down to
+  // the loads of that chunk, however far ahead the ring runs.  The hidden chunks therefore travel HD
+  // chunks ahead in registers, so that nothing younger than about PF k-steps is ever waited for.
+  constexpr int HD = S::HDEPTH;                       // chunks a hidden chunk waits in registers
+  u32x4 hreg[HD][NPASS];
+  auto load_hidden = [&](int c, u32x4 (&dst)[NPASS]) {      // chunk at walk position c (zeros past the end)
+    const unsigned k = (unsigned)(chunk_at(c < NCH ? c : 0) * S::KC) + 8u * pc;
+    const unsigned kc = min(k, klast);
 #pragma unroll
-      for (int i = 0; i < NPASS; ++i) dst[i] = *reinterpret_cast<const u32x4*>(a.hidden + (hoff[i] + kc));
-    };
-    auto keep_mask = [&](int c) -> unsigned {
-      const unsigned k = (unsigned)(chunk_at(c < NCH ? c : 0) * S::KC) + 8u * pc;
-      return (c < NCH && k < (unsigned)a.Hd) ? 0xffffffffu : 0u;
-    };
+    for (int i = 0; i < NPASS; ++i) dst[i] = *reinterpret_cast<const u32x4*>(a.hidden + (hoff[i] + kc));
+  };
+  auto keep_mask = [&](int c) -> unsigned {
+    const unsigned k = (unsigned)(chunk_at(c < NCH ? c : 0) * S::KC) + 8u * pc;
+    return (c < NCH && k < (unsigned)a.Hd) ? 0xffffffffu : 0u;
+  };
 #pragma unroll
-    for (int d = 1; d < HD; ++d) load_hidden(1 + d, hreg[d % HD]);     // chunks 2 .. HD: as if asked for earlier
-    // the last chunk's worth of W after them, the order that the loop leaves: with the hidden chunk as the youngest
-    // load the wait counts of the first chunk of every trip would cover for that (9 instead of 20)
-    __builtin_amdgcn_sched_barrier(0);
-    load_w_first(S::PF - S::KSTEPS, S::PF);
-    for (int cb = 0; cb < NCHU; cb += S::U) {
+  for (int d = 1; d < HD; ++d) load_hidden(1 + d, hreg[d % HD]);     // chunks 2 .. HD: as if asked for earlier
+  // the last chunk's worth of W after them, the order that the loop leaves: with the hidden chunk as the youngest
+  // load the wait counts of the first chunk of every trip would cover for that (9 instead of 20)
+  __builtin_amdgcn_sched_barrier(0);
+  load_w_first(S::PF - S::KSTEPS, S::PF);
+  for (int cb = 0; cb < NCHU; cb += S::U) {
 #pragma unroll
-      for (int uu = 0; uu < S::U; ++uu) {
-        const int c = cb + uu;
-        // One wave per SIMD: whatever is issued between two matrix instructions beyond their 16 cycles leaves the pipe
-        // idle, so a chunk's other work is dealt out among them, one piece per group of WNB: in the first k-step the
-        // loads of hidden chunk c + 1 + HD, in the last the LDS stores of chunk c + 2 (asked for HD - 1 chunks ago)
-        // into the free stage, behind a k-step's last group its operands' successors.
-        const unsigned kh = (unsigned)(chunk_at(c + 1 + HD < NCH ? c + 1 + HD : 0) * S::KC) + 8u * pc;
-        const unsigned khc = min(kh, klast);
-        // pieces past Hd become zeros by masking, not by a select: a select would let the compiler turn the loads
-        // into conditional ones and sink them down to the stores
-        const unsigned keep = keep_mask(c + 2);
+    for (int uu = 0; uu < S::U; ++uu) {
+      const int c = cb + uu;
+      // One wave per SIMD: whatever is issued between two matrix instructions beyond their 16 cycles leaves the pipe
+      // idle, so a chunk's other work is dealt out among them, one piece per group of WNB: in the first k-step the
+      // loads of hidden chunk c + 1 + HD, in the last the LDS stores of chunk c + 2 (asked for HD - 1 chunks ago)
+      // into the free stage, behind a k-step's last group its operands' successors.
+      const unsigned kh = (unsigned)(chunk_at(c + 1 + HD < NCH ? c + 1 + HD : 0) * S::KC) + 8u * pc;
+      const unsigned khc = min(kh, klast);
+      // pieces past Hd become zeros by masking, not by a select: a select would let the compiler turn the loads
+      // into conditional ones and sink them down to the stores
+      const unsigned keep = keep_mask(c + 2);
 #pragma unroll
-        for (int ks = 0; ks < S::KSTEPS; ++ks) {
-          const int slot_a = (uu * S::KSTEPS + ks) % S::PF;
-          const int gn = uu * S::KSTEPS + ks + S::PF;   // relative to the trip's first k-step
-          const long long wnext = (long long)wks * kstep_at(cb + gn / S::KSTEPS, gn % S::KSTEPS);
+      for (int ks = 0; ks < S::KSTEPS; ++ks) {
+        const int slot_a = (uu * S::KSTEPS + ks) % S::PF;
+        const int gn = uu * S::KSTEPS + ks + S::PF;   // relative to the trip's first k-step
+        const long long wnext = (long long)wks * kstep_at(cb + gn / S::KSTEPS, gn % S::KSTEPS);
 #pragma unroll
-          for (int jb = 0; jb < JB; ++jb) {
-            const int t = ks * JB + jb, tn = t + S::DB;
-            const int slot_b = (uu * CH + t) % S::DB;
-            const bf16x8 bop = bq[slot_b];
-            bq[slot_b] = tn < CH ? read_b(cur_off, tn / JB, tn % JB)
-                                 : read_b(nxt_off, (tn - CH) / JB, (tn - CH) % JB);
-            if (ks == 0 && jb < NPASS)
-              hreg[uu % HD][jb] = *reinterpret_cast<const u32x4*>(a.hidden + (hoff[jb] + khc));
-            if (ks == S::KSTEPS - 1 && jb < NPASS)
-              *reinterpret_cast<u32x4*>(stage + wr_off + soff[jb]) = hreg[(uu + 1) % HD][jb] & u32x4{keep, keep, keep, keep};
+        for (int jb = 0; jb < JB; ++jb) {
+          const int t = ks * JB + jb, tn = t + S::DB;
+          const int slot_b = (uu * CH + t) % S::DB;
+          const bf16x8 bop = bq[slot_b];
+          bq[slot_b] = tn < CH ? read_b(cur_off, tn / JB, tn % JB)
+                               : read_b(nxt_off, (tn - CH) / JB, (tn - CH) % JB);
+          if (ks == 0 && jb < NPASS)
+            hreg[uu % HD][jb] = *reinterpret_cast<const u32x4*>(a.hidden + (hoff[jb] + khc));
+          if (ks == S::KSTEPS - 1 && jb < NPASS)
+            *reinterpret_cast<u32x4*>(stage + wr_off + soff[jb]) = hreg[(uu + 1) % HD][jb] & u32x4{keep, keep, keep, keep};
 #pragma unroll
-            for (int ib = 0; ib < WNB; ++ib) {
-              if (uu == S::U - 1 && ks == S::KSTEPS - 1 && jb == JB - 1 && ib == WNB - 1)     // the trip's last
-                mfma_acc<true>(acc[ib][jb], abuf[slot_a][ib], bop);
-              else
-                mfma_acc<false>(acc[ib][jb], abuf[slot_a][ib], bop);
-              // The last group has read the operand: the load PF steps ahead goes into the same registers.  (Asked for
-              // before the matrix instructions it needed registers of its own, and the copies that rotate those into
-              // place at the loop's end waited for every load in flight, once per trip.)
-              if (jb == JB - 1) {
-                __builtin_amdgcn_sched_barrier(0);
-                abuf[slot_a][ib] = load_w<PACKED>(wrow[ib] + wnext);
-                __builtin_amdgcn_sched_barrier(0);
-              }
+          for (int ib = 0; ib < WNB; ++ib) {
+            if (uu == S::U - 1 && ks == S::KSTEPS - 1 && jb == JB - 1 && ib == WNB - 1)     // the trip's last
+              mfma_acc<true>(acc[ib][jb], abuf[slot_a][ib], bop);
+            else
+              mfma_acc<false>(acc[ib][jb], abuf[slot_a][ib], bop);
+            // The last group has read the operand: the load PF steps ahead goes into the same registers.  (Asked for
+            // before the matrix instructions it needed registers of its own, and the copies that rotate those into
+            // place at the loop's end waited for every load in flight, once per trip.)
+            if (jb == JB - 1) {
+              __builtin_amdgcn_sched_barrier(0);
+              abuf[slot_a][ib] = load_w<PACKED>(wrow[ib] + wnext);
+              __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);          // keep the ring's distance as written
           }
+          __builtin_amdgcn_sched_barrier(0);          // keep the ring's distance as written
         }
-        __syncthreads();
-        const unsigned tmp = cur_off; cur_off = nxt_off; nxt_off = wr_off; wr_off = tmp;
       }
+      __syncthreads();
+      const unsigned tmp = cur_off; cur_off = nxt_off; nxt_off = wr_off; wr_off = tmp;
     }
   }
 
@@ -350,7 +342,7 @@ __device__ __forceinline__ void lm_head_rows_tile(const LmHeadArgs& a, unsigned 
 }
 
 template <int BM, int WNB, int PF_, bool PACKED>
-__global__ __launch_bounds__(kLmThreads, (LmShape<BM, WNB, PF_>::MIN_WAVES)) void lm_head_rows_kernel(LmHeadArgs a) {
+__global__ __launch_bounds__(kLmThreads, 1) void lm_head_rows_kernel(LmHeadArgs a) {
   using S = LmShape<BM, WNB, PF_>;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   unsigned char* stage = lds_raw;                                          // NST x kLmStageBytes

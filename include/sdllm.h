@@ -246,8 +246,9 @@ int sdllm_lm_head_unmask(const sdllm_lm_head_params* p,
 /* Launch plan the library would use for these parameters (host only, no HIP call).  The masked count is
  * device data, so a call launches every kernel shape that B*K admits and the masked count found on the
  * device decides which of them does the work (the others exit at once): up to 32, 33..64 and 65..128 masked
- * positions take three kernels that stream W once with every position resident, more take 256-position row
- * chunks.  The plan describes the shape that serves B*K masked positions: rows of hidden per row chunk,
+ * positions take three kernels that stream W once with every position resident, more take row chunks of 160,
+ * 192, 224 or 256 positions, as few as their number allows and evenly filled.  The plan describes the shape that
+ * serves B*K masked positions: the most rows of hidden a row chunk takes (256 for the last shape),
  * rows of W per vocabulary tile, number of tiles, row chunks in the grid, workgroups launched, LDS bytes
  * per workgroup; triples_per_position is the workspace's row length (the largest tile count among the
  * shapes launched).  Returns SDLLM_OK or the validation error. */
@@ -355,10 +356,12 @@ typedef struct sdllm_attn_plan {
   int32_t kv_splits;
   int32_t rows_per_workgroup;
   int32_t workgroups;
-  int32_t key_tiles_per_split;
-  int32_t workgroup_shape;   /* 0: 4 waves; 1: 8 waves, two groups on the same rows alternating key tiles;
-                                2: 8 waves, two groups on different rows sharing every key tile (bf16 only) */
-  int32_t ring_stages;       /* K/V tiles the LDS ring of a workgroup holds per group (2..4) */
+  int32_t key_tiles_per_split; /* bf16: 64-key tiles; fp32: 16-key blocks of the whole sequence */
+  int32_t workgroup_shape;   /* bf16: 0: 4 waves; 1: 8 waves, two groups on the same rows alternating key tiles;
+                                2: 8 waves, two groups on different rows sharing every key tile.
+                                fp32: 0 (1 to 8 waves) */
+  int32_t ring_stages;       /* bf16: K/V tiles the LDS ring of a workgroup holds per group (2..4).
+                                fp32: 2 (no ring in LDS: a key block in use and the next one, in registers) */
 } sdllm_attn_plan;
 
 int sdllm_plan_attention(const sdllm_attn_params* p, sdllm_attn_plan* plan);

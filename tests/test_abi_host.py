@@ -178,6 +178,23 @@ def test_plan_invariants_over_random_parameters(lib):
     assert seen == {0, 1, 2}
 
 
+def test_fp32_plan_is_consistent(lib):
+    """Host-only: the fp32 plan's fields as the header describes them, over seeded random parameter sets."""
+    import numpy as np
+    g = np.random.Generator(np.random.Philox(key=32))
+    for _ in range(400):
+        D = 4 * int(g.integers(1, 65)); Hkv = int(g.integers(1, 33)); ratio = int(g.choice([1, 2, 7, 64]))
+        B = int(2 ** g.uniform(0, 12)); K = int(g.integers(1, 70)); P = int(2 ** g.uniform(0, 13)); s = int(g.choice([0, 1, 40]))
+        p = sd.attn_params(sd.FP32, B, ratio * Hkv, Hkv, D, P, P, K, s, s)
+        pl = sd.plan_attention(p)
+        assert (pl.kv_splits, pl.workgroup_shape, pl.ring_stages) == (1, 0, 2)
+        assert pl.key_tiles_per_split == -(-(P + K + s) // 16)
+        assert pl.rows_per_workgroup in ((16, 32, 64, 128) if D <= 128 else (16, 32, 64))
+        tiles = -(-ratio * (K + s) // pl.rows_per_workgroup)
+        assert B * Hkv * tiles <= pl.workgroups <= (B * Hkv + 7) * tiles
+        assert sd.attention_workspace_bytes(p) == 0
+
+
 def test_plan_picks_the_workgroup_shape_from_the_parameters(lib):
     """Host-only: which of the three workgroup shapes a launch takes.  One workgroup per CU at most and splits
     of >= 4 key tiles: two groups on the same rows; K/V heads with >= 512 query rows: two groups on different rows

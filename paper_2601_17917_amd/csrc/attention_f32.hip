@@ -18,7 +18,7 @@
 //                 load of a V row serves the four blocks j.
 // What bounds it: the matrix pipe in principle (256 flop / cycle / CU in fp32, 157 TFLOP/s; two waves per SIMD cover each
 // other's softmax and load latency), at layer sizes the fixed parts of a short launch.  Measured, B2, 32 query / 8 KV heads
-// x 128, 64 query rows x 672 keys: 26 us (55 TFLOP/s, matrix pipe 40 % busy) against 276 us for one query row per wave
+// x 128, 64 query rows x 672 keys: 26 us (53 TFLOP/s, matrix pipe 34 % busy) against 276 us for one query row per wave
 // with fp32 FMAs out of LDS; B1, 4 heads x 64, 48 x 112: 7.2 against 17.5 us.
 #include "common.h"
 #include <algorithm>

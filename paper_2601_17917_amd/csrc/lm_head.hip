@@ -128,9 +128,9 @@ __device__ __forceinline__ void mfma_acc(f32x4& acc, const bf16x8& a, const bf16
 // PACKED: W is the packed image (a lane's operand pieces of consecutive k-steps are 1 KB apart, a wave's load is
 // one contiguous kilobyte that no other load touches: nontemporal)
 // Bound by the matrix pipe as one wave per SIMD can keep it busy, and by the stream of W under it.  Per call over
-// 126464 x 4096, packed W, full 256-row chunks and loads issued in bursts before / as it is now:
-//   160 masked positions 279 / 203 us, 256: 299 / 270, 282: 510 / 350, 384: 509 / 405, 512: 539 / 496 (1.07 PFLOP/s)
-// and row-major W: 160 positions 315 / 245 us, 256: 306 / 289, 282: 549 / 420, 512: 558 / 520.
+// 126464 x 4096, packed W, full 256-row chunks and loads issued in bursts before / as it is now, in turn on one card:
+//   160 masked positions 287 / 200 us, 256: 287 / 269, 282: 511 / 337, 384: 508 / 388, 512: 539 / 482 (1.10 PFLOP/s)
+// and row-major W: 160 positions 325 / 264 us, 256: 316 / 282, 282: 530 / 420, 384: 540 / 459, 512: 548 / 511.
 template <int BM, int WNB, int PF_, bool PACKED, int JB>
 __device__ __forceinline__ void lm_head_rows_tile(const LmHeadArgs& a, unsigned char* stage, const int* row_of,
                                                   Partial* red, int tile) {
@@ -300,13 +300,15 @@ __device__ __forceinline__ void lm_head_rows_tile(const LmHeadArgs& a, unsigned 
 
   // ---- row reduction of the tile: the maximum over this lane's vocabulary ids and the four lane groups first, so that
   // every exponential is taken relative to it and the rest are plain sums (one pairwise merge per exchange through the
-  // LDS crossbar before: 126464 x 4096 packed, 256 positions 278 -> 270 us, 512: 498 -> 494); then over the waves
+  // LDS crossbar before: 126464 x 4096 packed, 256 positions 278 -> 270 us, 512: 498 -> 494); then over the waves.
+  // Ids past V are selected away by the lane's distance to the end: under a branch around each row block's values the
+  // compiler copied accumulators out for both arms (33 registers spilled; row-major, 256 positions 288 -> 283 us without)
   const int n0 = tile * S::BN + wave * (WNB * 16) + 4 * q;     // this lane's ids: n0 + 16 ib + r
   const int left = a.V - n0;                                   // the last tile may run past V
 #pragma unroll
   for (int jb = 0; jb < JB; ++jb) {
-    // this row block's accumulators leave the accumulation registers here: copied out earlier, up to 33 registers of
-    // the 16-block tile went to scratch memory
+    // this row block's accumulators leave the accumulation registers here, not earlier: one or two registers of the
+    // 16-block tile went to scratch memory without it
 #pragma unroll
     for (int ib = 0; ib < WNB; ++ib) asm volatile("" : "+a"(acc[ib][jb]));
     float v[WNB * 4];

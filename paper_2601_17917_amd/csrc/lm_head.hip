@@ -3,26 +3,14 @@
 // (max, sum of exp, lowest argmax id) triples in registers; they are never written to memory.
 // The triples go to the same commit kernel as those of the streaming reduction over stored logits.
 //
-// One workgroup = one vocabulary tile (BN rows of W) x one chunk of masked rows (at most 256), the whole of Hd.
-//   * Masked rows are compacted inside the kernel (every workgroup scans the mask bytes), so the
-//     matrix cores only see rows that Eq. 4 asks for; a chunk beyond the masked count exits at once.
-//   * W is the streamed operand and has no reuse inside a workgroup: every wave owns WNB x 16
-//     vocabulary rows and loads its MFMA A operands straight from global memory into registers
-//     (16 bytes per lane = the operand layout itself), PF k-steps ahead; W never touches LDS.
-//   * The hidden rows are the shared operand: chunks of KC elements per row go through an LDS ring
-//     (registers -> LDS ahead of use, one barrier per chunk), XOR-swizzled so that the 16-byte
-//     B-operand reads are bank-conflict free.
-//   * logits^T tile = W_tile h^T (v_mfma_f32_16x16x32_bf16, fp32 accumulate): a lane ends up with
-//     vocabulary ids 4 (lane / 16) + r of row lane % 16, so the row reduction is in-lane first, then two
-//     lane exchanges, then across the four waves through LDS.
-//   * Row chunks of one vocabulary tile get workgroup ids that are equal mod 8 and adjacent in
-//     dispatch order: same XCD, same L2, so W comes from HBM once.
-//   * Shapes: more than 128 masked positions go to lm_head_rows_kernel in chunks of 160 to 256 rows.  It is bound by
-//     the matrix pipe (one wave per SIMD, accumulators in the accumulation registers, B operands through
-//     a register ring fed across chunk boundaries).  Calls with at most 128 masked positions are a read
-//     of W and take the stream kernels further down, which turn the roles around: the hidden operands
-//     stay in registers and W goes through LDS (1 KB row pieces through registers up to 64 positions,
-//     global -> LDS transfers up to 128), or, when W is the packed image, comes straight from it.
+//   * Masked rows are compacted inside the kernels (every workgroup scans the mask bytes), so the matrix cores only see rows
+//     that Eq. 4 asks for.
+//   * logits^T tile = W_tile h^T (v_mfma_f32_16x16x32_bf16, fp32 accumulate): a lane ends up with vocabulary ids
+//     4 (lane / 16) + r of row lane % 16, so the row reduction is in-lane first, then two lane exchanges.
+//   * Shapes: more than 128 masked positions go to lm_head_rows_kernel in chunks of 160 to 256 rows, a tiled product with both
+//     operands in LDS.  Calls with at most 128 masked positions are a read of W and take the stream kernels further down,
+//     which turn the roles around: the hidden operands stay in registers and W goes through LDS (1 KB row pieces through
+//     registers up to 64 positions, global -> LDS transfers up to 128), or, when W is the packed image, comes straight from it.
 //   * The masked count is device data: the host launches every shape that B x K admits and each launch
 //     exits unless the count is in its range.
 #include "common.h"
@@ -37,7 +25,6 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kLmThreads = 256;
 constexpr int kLmWaves = kLmThreads / 64;
-constexpr int kLmStageBytes = 32768;      // one LDS stage of hidden rows
 
 struct LmHeadArgs {
   const uint16_t* hidden;     // [rows_total][ld_h]
@@ -47,7 +34,7 @@ struct LmHeadArgs {
   long long ld_h, ld_w;       // elements
   int rows_total, V, Hd;
   int ntile;                  // vocabulary tiles
-  int nchunk;                 // row chunks in the grid (upper bound of ceil(masked rows / BM))
+  int nchunk;                 // row chunks in the grid (upper bound of ceil(masked rows / kRwBM))
   // The masked count is device data, the shape that suits it is not known to the host: a call launches every
   // shape its B x K admits and each launch exits at once unless min_masked <= masked count <= max_masked.
   int min_masked, max_masked;
@@ -66,51 +53,49 @@ __device__ __forceinline__ void store_partial(const LmHeadArgs& a, int row, int 
 
 // Number of masked positions of the call (uniform over the workgroup): one pass over the mask bytes without
 // barriers, then one reduction.  wsum: kLmWaves ints of LDS, free for other use on return.
+template <int THREADS = kLmThreads>
 __device__ __forceinline__ int lm_masked_count(const LmHeadArgs& a, int* wsum) {
   const int tid = threadIdx.x;
   int mine = 0;
-  for (int i = tid; i < a.rows_total; i += kLmThreads) mine += a.masked[i] != 0;
+  for (int i = tid; i < a.rows_total; i += THREADS) mine += a.masked[i] != 0;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) mine += __shfl_xor(mine, off);
   if ((tid & 63) == 0) wsum[tid >> 6] = mine;
   __syncthreads();
   int total = 0;
 #pragma unroll
-  for (int w = 0; w < kLmWaves; ++w) total += wsum[w];
+  for (int w = 0; w < THREADS / 64; ++w) total += wsum[w];
   __syncthreads();
   return total;
 }
 
-
-// lm_head_rows_kernel: BM rows of positions per chunk at most, WNB 16-row blocks of W per wave, PF k-steps of W in flight
-// per wave.  It is bound by the matrix pipe with one wave per SIMD.  Its accumulators (256 registers for a full chunk) sit
-// in the accumulation half of the register file by construction (left to the register allocator they were shuffled
-// between the halves inside the loop, or spilled), and its B operands run through a register ring DB deep that is fed
-// across chunk boundaries, which takes a third LDS stage (a chunk is complete one barrier before it is first read).
-template <int BM, int WNB, int PF_>
-struct LmShape {
-  static constexpr int BN = kLmWaves * WNB * 16;            // vocabulary rows per workgroup
-  static constexpr int KC = kLmStageBytes / 2 / BM;         // hidden elements per row and stage
-  static constexpr int KSTEPS = KC / 32;                    // MFMA k-steps per stage
-  static constexpr int PIECES = KC / 8;                     // 16-byte pieces per LDS row
-  static constexpr int PF = PF_;                            // k-steps of W in flight per wave
-  static constexpr int U = PF / KSTEPS;                     // chunks per unrolled loop body (static ring slots)
-  static constexpr int ROWS_PER_PASS = kLmThreads / PIECES; // rows one staging pass of the workgroup covers
-  static constexpr int NST = 3;
-  static constexpr int DB = 8;
-  static constexpr int HDEPTH = 4 / KSTEPS;                 // chunks a hidden chunk waits in registers
-  static_assert(PIECES == 8 && kLmThreads % PIECES == 0, "shape (swz)");
-  static_assert(KSTEPS > 1 && PF > KSTEPS && (KSTEPS * U) % PF == 0 && U % 2 == 0 && U % HDEPTH == 0, "ring");
-  // LDS rows are unpadded; piece p of row r sits at slot swz(r, p), chosen so that the 16 lanes of a
-  // B-operand read (rows r..r+15, same piece) fall into 16 different 16-byte bank groups
-  __device__ static __forceinline__ int swz(int r, int p) { return p ^ ((r >> 1) & 7); }
-};
-
-template <bool NT = false>
-__device__ __forceinline__ bf16x8 load_w(const uint16_t* p) {
-  if constexpr (NT) return __builtin_bit_cast(bf16x8, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)));
-  else return *reinterpret_cast<const bf16x8*>(p);
+template <int N> __device__ __forceinline__ void lm_wait_vmcnt() {
+  static_assert(N >= 0 && N <= 63, "vmcnt is a six-bit field");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));    // expcnt / lgkmcnt: no wait
 }
+// one transfer: lane i's 16 bytes at vaddr land at lds_addr + 16 i (lds_addr uniform)
+template <bool NT>
+__device__ __forceinline__ void lm_dma16(unsigned lds_addr, const void* vaddr) {
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
+                 :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(vaddr) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(vaddr) : "memory", "m0");
+}
+
+// lm_head_rows_kernel: 512 threads, two waves per SIMD.  A workgroup owns 256 vocabulary rows x JB 16-row blocks of
+// positions; wave (wv, wp) owns four 16-row blocks of W x half of the position blocks.  Both operands go from global memory
+// straight into LDS, 64 elements of Hd (two k-steps) per ring stage: three stages of W, two of the hidden rows.
+constexpr int kRwThreads = 512;
+constexpr int kRwWaves = kRwThreads / 64;
+constexpr int kRwBM = 256;                       // most positions of a workgroup
+constexpr int kRwBN = 256;                       // vocabulary rows of a workgroup
+constexpr int kRwStage = 256 * 128;              // 32 KB: one stage of either operand
+constexpr int kRwWNST = 3, kRwHNST = 2;
+constexpr int kRwHid = kRwWNST * kRwStage;       // byte offset of the hidden stages
+constexpr int kRwLds = (kRwWNST + kRwHNST) * kRwStage;
+static_assert(kRwLds <= 160 * 1024, "LDS of a CU");
 
 // acc += A B with the accumulator pinned to the accumulation registers.  The compiler does not see a matrix instruction
 // inside the asm statement and puts no wait states behind it.  Between matrix instructions none are needed; the LAST one
@@ -124,258 +109,263 @@ __device__ __forceinline__ void mfma_acc(f32x4& acc, const bf16x8& a, const bf16
   else asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 
-// One (vocabulary tile, row chunk) of lm_head_rows_kernel: JB 16-row blocks of positions.
-// PACKED: W is the packed image (a lane's operand pieces of consecutive k-steps are 1 KB apart, a wave's load is
-// one contiguous kilobyte that no other load touches: nontemporal)
-// Bound by the matrix pipe as one wave per SIMD can keep it busy, and by the stream of W under it.  Per call over
-// 126464 x 4096, packed W, full 256-row chunks and loads issued in bursts before / as it is now, in turn on one card:
-//   160 masked positions 287 / 200 us, 256: 287 / 269, 282: 511 / 337, 384: 508 / 388, 512: 539 / 482 (1.10 PFLOP/s)
-// and row-major W: 160 positions 325 / 264 us, 256: 316 / 282, 282: 530 / 420, 384: 540 / 459, 512: 548 / 511.
-template <int BM, int WNB, int PF_, bool PACKED, int JB>
-__device__ __forceinline__ void lm_head_rows_tile(const LmHeadArgs& a, unsigned char* stage, const int* row_of,
-                                                  Partial* red, int tile) {
-  using S = LmShape<BM, WNB, PF_>;
-  static_assert(JB % 2 == 0 && JB * 16 <= BM, "whole staging passes, rows that the LDS layout holds");
-  constexpr int NPASS = JB * 16 / S::ROWS_PER_PASS;            // 16-byte staging loads per thread and chunk
+// The vocabulary tiles tile0, tile0 + tile_step, ... for one row chunk of JB 16-row blocks of positions.
+// Between its roofs: 256 positions x 126464 x 4096 take 421k cycles, of which the matrix pipe is busy 253k, at a clock that falls
+// to 2.1 GHz and below under matrix work on a full stream of W; without the transfers 389k cycles, without the matrix
+// instructions 180 us at 2.4 GHz.  What this split gains over one wave per SIMD with W straight into registers: whole
+// 128-byte lines of both operands (16 rows x 64 bytes a transfer took 1.5 times as long), two waves per SIMD that fill each
+// other's gaps, one prologue per workgroup instead of one per tile.  Per call over 126464 x 4096, before / after in turn on one
+// card: row-major W 160 positions 263 / 213 us, 256: 282 / 249, 282: 412 / 313, 384: 443 / 357, 512: 503 / 454 (1.17 PFLOP/s);
+// packed 200 / 192, 264 / 250, 344 / 308, 381 / 348, 478 / 445.
+template <bool PACKED, int JB>
+__device__ __forceinline__ void lm_head_rows_tiles(const LmHeadArgs& a, unsigned char* lds, const int* row_of,
+                                                   int tile0, int tile_step) {
+  static_assert(JB % 2 == 0 && JB * 16 <= kRwBM, "two halves");
+  constexpr int JH = JB / 2;                     // position blocks per wave
+  constexpr int NH = (2 * JB + kRwWaves - 1) / kRwWaves;       // hidden transfers per wave and stage, at most
+  static_assert(NH <= 4 && JH >= 4, "one transfer per group of matrix instructions");
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-
-  // ---- operand addressing
-  const int NK = a.Hd / 32;                                    // k-steps
-  const int NCH = (NK + S::KSTEPS - 1) / S::KSTEPS;            // LDS chunks
+  const int wv = wave & 3, wp = wave >> 2;
   const int q = lane >> 4, l16 = lane & 15;
-  // every workgroup walks the chunks of Hd in its own rotation, so that the workgroups resident at one
-  // time do not all ask for the same columns of W at once
-  const int c0 = tile % NCH;
-  auto chunk_at = [&](int c) { int ch = c + c0; ch -= (ch >= NCH) ? NCH : 0; return ch; };   // c < NCH
-  auto kstep_at = [&](int c, int ss) {                         // k-step ss of the chunk at walk position c; past the
-    return min(chunk_at(min(c, NCH - 1)) * S::KSTEPS + ss, NK - 1);   // end any valid one
-  };
-  const uint16_t* wrow[WNB];                                   // this lane's operand piece of k-step 0
-  constexpr int wks = PACKED ? 512 : 32;                       // elements from one k-step's piece to the next
-#pragma unroll
-  for (int ib = 0; ib < WNB; ++ib) {
-    if constexpr (PACKED) {
-      const int nb = min(tile * (S::BN / 16) + wave * WNB + ib, (a.V + 15) / 16 - 1);   // blocks past V: the last one
-      wrow[ib] = a.weight + ((long long)nb * NK * 64 + lane) * 8;
-    } else {
-      const int n = min(tile * S::BN + (wave * WNB + ib) * 16 + l16, a.V - 1);   // rows past V: any valid row
-      wrow[ib] = a.weight + (long long)n * a.ld_w + 8 * q;
-    }
-  }
-  // staging: this thread moves piece `pc` of rows srow0 + ROWS_PER_PASS * i
-  const int pc = tid % S::PIECES, srow0 = tid / S::PIECES;
-  unsigned hoff[NPASS];          // element offset of the thread's rows
-  unsigned soff[NPASS];          // byte offset inside a stage
-#pragma unroll
-  for (int i = 0; i < NPASS; ++i) {
-    const int r = srow0 + S::ROWS_PER_PASS * i;
-    hoff[i] = (unsigned)((long long)max(row_of[r], 0) * a.ld_h);
-    soff[i] = (unsigned)(r * S::KC * 2 + (S::swz(r, pc) << 4));
-  }
-  // B-operand read of 16-row block jb, k-step ks: row jb * 16 + l16, piece 4 ks + q
-  const unsigned boff = (unsigned)(l16 * S::KC * 2);
+  const unsigned lds_wave = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)lds + wave * 1024;
+  const int NK = a.Hd / 32, NP = (NK + 1) / 2;   // k-steps, pairs of them
 
-  f32x4 acc[WNB][JB];
+  // ---- transfers.  Row-major operands: a transfer is 8 rows x 128 bytes (whole lines); transfer 2 b + h brings rows
+  // 8 h .. 8 h + 7 of 16-row block b.  Lane i lands at 16 i, that is place i / 8 of the kilobyte's 8 row places, slot i % 8.
+  // Place g holds row 8 h + g / 2 + 4 (g % 2), slot s piece s ^ (row % 4 + 4 h) of the pair's eight 16-byte pieces.  The 16
+  // lanes that an operand read serves at a time are 0-3, 12-15, 20-27 (and 4-11, 16-19, 28-31; the same 32 higher), rows
+  // 0-3, 12-15 of one piece and 4-11 of the next: with this order they fall into 16 different 16-byte groups of banks, as
+  // 16 rows of one piece do.  (Place g = row % 8, xor 1 in the second half, slot = piece ^ (row % 8), free of conflicts
+  // only for 16 consecutive lanes, cost 4 cycles a read.)
+  // Packed W: a transfer is one operand tile, block b and k-step h of the pair.
+  // This wave brings transfers wave, wave + 8, wave + 16, wave + 24 of either operand.
+  const unsigned klast = (unsigned)(a.Hd - 8);
+  const int g = lane >> 3, h = wave & 1;         // kRwWaves is even: h is the same for all of a wave's transfers
+  const int r8 = (g >> 1) + 4 * (g & 1);
+  const unsigned piece = (unsigned)(8 * ((lane & 7) ^ ((g >> 1) + 4 * h)));    // elements
+  const uint16_t* wsrc[4];
+  auto w_tile = [&](int tile) {                  // W's transfers bring this tile from here on
 #pragma unroll
-  for (int ib = 0; ib < WNB; ++ib)
-#pragma unroll
-    for (int jb = 0; jb < JB; ++jb) acc[ib][jb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // ---- prologue: first W k-steps in flight, first hidden chunk(s) into LDS
-  bf16x8 abuf[S::PF][WNB];
-  auto load_w_first = [&](int s0, int s1) {
-#pragma unroll
-    for (int s = 0; s < S::PF; ++s)
-#pragma unroll
-      for (int ib = 0; ib < WNB; ++ib)
-        if (s >= s0 && s < s1)
-          abuf[s][ib] = load_w<PACKED>(wrow[ib] + (long long)wks * kstep_at(s / S::KSTEPS, s % S::KSTEPS));
-  };
-  load_w_first(0, S::PF - S::KSTEPS);
-  // A chunk's pieces past Hd are staged as zeros and its k-steps past Hd are computed like the others
-  // (finite W times zero adds nothing): the loop body has no branch, so the compiler's wait counters
-  // see one straight line and keep the W loads PF steps ahead.
-  const unsigned klast = (unsigned)(a.Hd - 8);          // last whole piece of a row
-  auto stage_now = [&](int c, unsigned char* dst) {     // chunk at walk position c straight into LDS
-    const unsigned k = (unsigned)(chunk_at(c < NCH ? c : 0) * S::KC) + 8u * pc;
-    const bool keep = c < NCH && k < (unsigned)a.Hd;
-#pragma unroll
-    for (int i = 0; i < NPASS; ++i) {
-      const u32x4 v = *reinterpret_cast<const u32x4*>(a.hidden + (hoff[i] + min(k, klast)));
-      *reinterpret_cast<u32x4*>(dst + soff[i]) = keep ? v : u32x4{0u, 0u, 0u, 0u};
-    }
-  };
-  stage_now(0, stage);
-  stage_now(1, stage + kLmStageBytes);
-  __syncthreads();
-
-  const int NCHU = (NCH + S::U - 1) / S::U * S::U;      // chunks past NCH see zeros
-  // ---- main loop: three LDS stages (read c, already complete c + 1, being written c + 2)
-  constexpr int CH = S::KSTEPS * JB;                  // B operands per chunk
-  static_assert(S::U * CH % S::DB == 0 && S::DB <= CH, "B ring");
-  unsigned pv[S::KSTEPS];                             // per-lane part of a B-operand address, by k-step
-#pragma unroll
-  for (int ks = 0; ks < S::KSTEPS; ++ks) pv[ks] = boff + (unsigned)(S::swz(l16, 4 * ks + q) << 4);
-  auto read_b = [&](unsigned st_off, int ks, int jb) {
-    return *reinterpret_cast<const bf16x8*>(stage + st_off + pv[ks] + jb * 16 * S::KC * 2);
-  };
-  unsigned cur_off = 0, nxt_off = kLmStageBytes, wr_off = 2 * kLmStageBytes;    // uniform
-  bf16x8 bq[S::DB];
-#pragma unroll
-  for (int d = 0; d < S::DB; ++d) bq[d] = read_b(cur_off, d / JB, d % JB);
-  // Loads return in issue order, so waiting for a young load also waits for every older one: a hidden
-  // chunk that is consumed at the end of the chunk it was asked for in would drain the W ring down to
-  // the loads of that chunk, however far ahead the ring runs.  The hidden chunks therefore travel HD
-  // chunks ahead in registers, so that nothing younger than about PF k-steps is ever waited for.
-  constexpr int HD = S::HDEPTH;                       // chunks a hidden chunk waits in registers
-  u32x4 hreg[HD][NPASS];
-  auto load_hidden = [&](int c, u32x4 (&dst)[NPASS]) {      // chunk at walk position c (zeros past the end)
-    const unsigned k = (unsigned)(chunk_at(c < NCH ? c : 0) * S::KC) + 8u * pc;
-    const unsigned kc = min(k, klast);
-#pragma unroll
-    for (int i = 0; i < NPASS; ++i) dst[i] = *reinterpret_cast<const u32x4*>(a.hidden + (hoff[i] + kc));
-  };
-  auto keep_mask = [&](int c) -> unsigned {
-    const unsigned k = (unsigned)(chunk_at(c < NCH ? c : 0) * S::KC) + 8u * pc;
-    return (c < NCH && k < (unsigned)a.Hd) ? 0xffffffffu : 0u;
-  };
-#pragma unroll
-  for (int d = 1; d < HD; ++d) load_hidden(1 + d, hreg[d % HD]);     // chunks 2 .. HD: as if asked for earlier
-  // the last chunk's worth of W after them, the order that the loop leaves: with the hidden chunk as the youngest
-  // load the wait counts of the first chunk of every trip would cover for that (9 instead of 20)
-  __builtin_amdgcn_sched_barrier(0);
-  load_w_first(S::PF - S::KSTEPS, S::PF);
-  for (int cb = 0; cb < NCHU; cb += S::U) {
-#pragma unroll
-    for (int uu = 0; uu < S::U; ++uu) {
-      const int c = cb + uu;
-      // One wave per SIMD: whatever is issued between two matrix instructions beyond their 16 cycles leaves the pipe
-      // idle, so a chunk's other work is dealt out among them, one piece per group of WNB: in the first k-step the
-      // loads of hidden chunk c + 1 + HD, in the last the LDS stores of chunk c + 2 (asked for HD - 1 chunks ago)
-      // into the free stage, behind a k-step's last group its operands' successors.
-      const unsigned kh = (unsigned)(chunk_at(c + 1 + HD < NCH ? c + 1 + HD : 0) * S::KC) + 8u * pc;
-      const unsigned khc = min(kh, klast);
-      // pieces past Hd become zeros by masking, not by a select: a select would let the compiler turn the loads
-      // into conditional ones and sink them down to the stores
-      const unsigned keep = keep_mask(c + 2);
-#pragma unroll
-      for (int ks = 0; ks < S::KSTEPS; ++ks) {
-        const int slot_a = (uu * S::KSTEPS + ks) % S::PF;
-        const int gn = uu * S::KSTEPS + ks + S::PF;   // relative to the trip's first k-step
-        const long long wnext = (long long)wks * kstep_at(cb + gn / S::KSTEPS, gn % S::KSTEPS);
-#pragma unroll
-        for (int jb = 0; jb < JB; ++jb) {
-          const int t = ks * JB + jb, tn = t + S::DB;
-          const int slot_b = (uu * CH + t) % S::DB;
-          const bf16x8 bop = bq[slot_b];
-          bq[slot_b] = tn < CH ? read_b(cur_off, tn / JB, tn % JB)
-                               : read_b(nxt_off, (tn - CH) / JB, (tn - CH) % JB);
-          if (ks == 0 && jb < NPASS)
-            hreg[uu % HD][jb] = *reinterpret_cast<const u32x4*>(a.hidden + (hoff[jb] + khc));
-          if (ks == S::KSTEPS - 1 && jb < NPASS)
-            *reinterpret_cast<u32x4*>(stage + wr_off + soff[jb]) = hreg[(uu + 1) % HD][jb] & u32x4{keep, keep, keep, keep};
-#pragma unroll
-          for (int ib = 0; ib < WNB; ++ib) {
-            if (uu == S::U - 1 && ks == S::KSTEPS - 1 && jb == JB - 1 && ib == WNB - 1)     // the trip's last
-              mfma_acc<true>(acc[ib][jb], abuf[slot_a][ib], bop);
-            else
-              mfma_acc<false>(acc[ib][jb], abuf[slot_a][ib], bop);
-            // The last group has read the operand: the load PF steps ahead goes into the same registers.  (Asked for
-            // before the matrix instructions it needed registers of its own, and the copies that rotate those into
-            // place at the loop's end waited for every load in flight, once per trip.)
-            if (jb == JB - 1) {
-              __builtin_amdgcn_sched_barrier(0);
-              abuf[slot_a][ib] = load_w<PACKED>(wrow[ib] + wnext);
-              __builtin_amdgcn_sched_barrier(0);
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);          // keep the ring's distance as written
-        }
+    for (int i = 0; i < 4; ++i) {
+      const int blk = (wave + kRwWaves * i) >> 1;
+      if constexpr (PACKED) {
+        const int nb = min(tile * (kRwBN / 16) + blk, (a.V + 15) / 16 - 1);                // blocks past V: the last one
+        wsrc[i] = a.weight + ((long long)nb * NK * 64 + lane) * 8;
+      } else {
+        const int n = min(tile * kRwBN + blk * 16 + 8 * h + r8, a.V - 1);                  // rows past V: any valid row
+        wsrc[i] = a.weight + (long long)n * a.ld_w;
       }
-      __syncthreads();
-      const unsigned tmp = cur_off; cur_off = nxt_off; nxt_off = wr_off; wr_off = tmp;
     }
+  };
+  const uint16_t* hsrc[NH];
+#pragma unroll
+  for (int i = 0; i < NH; ++i) {
+    const int r = min(((wave + kRwWaves * i) >> 1) * 16 + 8 * h + r8, JB * 16 - 1);
+    hsrc[i] = a.hidden + (long long)max(row_of[r], 0) * a.ld_h;
   }
+  const int my_row = tid < JB * 16 ? row_of[tid] : -1;
+  __syncthreads();                               // the list's place in LDS belongs to the ring from here on
 
-  // ---- row reduction of the tile: the maximum over this lane's vocabulary ids and the four lane groups first, so that
-  // every exponential is taken relative to it and the rest are plain sums (one pairwise merge per exchange through the
-  // LDS crossbar before: 126464 x 4096 packed, 256 positions 278 -> 270 us, 512: 498 -> 494); then over the waves.
-  // Ids past V are selected away by the lane's distance to the end: under a branch around each row block's values the
-  // compiler copied accumulators out for both arms (33 registers spilled; row-major, 256 positions 288 -> 283 us without)
-  const int n0 = tile * S::BN + wave * (WNB * 16) + 4 * q;     // this lane's ids: n0 + 16 ib + r
-  const int left = a.V - n0;                                   // the last tile may run past V
+  // Every workgroup walks a tile's pairs in a rotation of the tile's, so that the workgroups resident at one time do not all
+  // ask for the same columns of W at once.  Pairs form one sequence over all of the workgroup's tiles: the transfers run ahead
+  // into the next tile; behind the last one they bring its last pair again (into stages that nobody reads any more).
+  struct Walk { int tile, left, pair; };         // pairs left in the tile, this one included
+  const int turn = tile_step % NP;               // from one tile's rotation to the next one's
+  const int last_tile = a.ntile - tile_step;     // tiles below it have a successor
+  auto next = [&](Walk& w) -> bool {             // true: a new tile.  By selects: branches here split the trip's halves
+    const bool end = w.left == 1, more = end && w.tile < last_tile;
+    const int p = w.pair + 1 + (more ? turn : 0);              // a tile's walk ends one pair before its first
+    w.pair = end && !more ? w.pair : p - (p >= NP ? NP : 0);
+    w.left = end ? (more ? NP : 1) : w.left - 1;
+    w.tile += more ? tile_step : 0;
+    return more;
+  };
+  auto issue_w = [&](int i, int pr, int stage_ofs) {           // transfer i (0..3) of pair pr
+    const unsigned dst = lds_wave + (unsigned)stage_ofs + kRwWaves * i * 1024;
+    if constexpr (PACKED) lm_dma16<true>(dst, wsrc[i] + (long long)min(2 * pr + h, NK - 1) * 512);
+    else lm_dma16<true>(dst, wsrc[i] + min(64u * pr + piece, klast));
+  };
+  auto issue_h = [&](int i, int pr, int stage_ofs) {           // transfer i (0..NH - 1), if this wave has it
+    const unsigned dst = lds_wave + kRwHid + (unsigned)stage_ofs + kRwWaves * i * 1024;
+    if ((i + 1) * kRwWaves <= 2 * JB || wave + kRwWaves * i < 2 * JB) lm_dma16<false>(dst, hsrc[i] + min(64u * pr + piece, klast));
+  };
+  // Where Hd ends in mid-pair (an odd number of k-steps), the hidden pieces past it, which the transfers filled with the row's
+  // last one, become zeros: this wave's own transfers, landed, before the barrier that hands them out.
+  auto zero_past_end = [&](int pr, int stage_ofs) {
+    if (2 * pr + 1 < NK) return;                 // uniform
+    if (64u * pr + piece <= klast) return;
 #pragma unroll
-  for (int jb = 0; jb < JB; ++jb) {
-    // this row block's accumulators leave the accumulation registers here, not earlier: one or two registers of the
-    // 16-block tile went to scratch memory without it
+    for (int i = 0; i < NH; ++i)
+      if ((i + 1) * kRwWaves <= 2 * JB || wave + kRwWaves * i < 2 * JB)
+        *reinterpret_cast<u32x4*>(lds + kRwHid + stage_ofs + (wave + kRwWaves * i) * 1024 + lane * 16) = u32x4{0u, 0u, 0u, 0u};
+  };
+
+  // ---- operand reads (two kilobytes per 16-row block and stage)
+  const unsigned rm = (unsigned)((l16 >> 3) * 1024 + (2 * (l16 & 3) + ((l16 >> 2) & 1)) * 128 +
+                                 ((q ^ ((l16 & 3) + 4 * (l16 >> 3))) << 4));
+  const unsigned char* abase[2];
+  const unsigned char* bbase[2];
 #pragma unroll
-    for (int ib = 0; ib < WNB; ++ib) asm volatile("" : "+a"(acc[ib][jb]));
-    float v[WNB * 4];
-#pragma unroll
-    for (int ib = 0; ib < WNB; ++ib)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) v[ib * 4 + r] = 16 * ib + r < left ? acc[ib][jb][r] : -INFINITY;
-    float m = kNegBig;
-#pragma unroll
-    for (int i = 0; i < WNB * 4; ++i) m = fmaxf(m, v[i]);
-    m = row_allreduce(m, [](float x, float y) { return fmaxf(x, y); });
-    int idx = 0x7fffffff;
-#pragma unroll
-    for (int i = WNB * 4 - 1; i >= 0; --i) idx = (v[i] == m) ? n0 + 16 * (i / 4) + i % 4 : idx;   // lowest id of a tie
-    idx = row_allreduce(idx, [](int x, int y) { return min(x, y); });
-    const float ml = m * kLog2e;
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < WNB * 4; ++i) s += fast_exp2(fmaf(v[i], kLog2e, -ml));
-    s = row_allreduce(s, [](float x, float y) { return x + y; });
-    if (q == 0) red[wave * BM + jb * 16 + l16] = Partial{m, s, idx};
+  for (int ks = 0; ks < 2; ++ks) {
+    abase[ks] = lds + wv * 8192 + (PACKED ? ks * 1024 + lane * 16 : rm ^ (ks << 6));
+    bbase[ks] = lds + kRwHid + wp * JH * 2048 + (rm ^ (ks << 6));
   }
-  __syncthreads();
-  if (tid < JB * 16 && row_of[tid] >= 0) {
-    Partial p = red[tid];
+  // The operands of the next k-step go in flight during this one.  The B operands are replaced in place, each behind the
+  // matrix instructions that read it; those of the last two groups and the A operands, which all groups read, have a second
+  // set, so that no read is asked for right before the barrier that waits for it.
+  constexpr int ND = 2, NPL = JH - ND;
+  f32x4 acc[4][JH];
+  bf16x8 av[2][4], bv[NPL], bd[2][ND];
+  auto step = [&](auto par_c, const unsigned char* an, const unsigned char* bn, auto transfer) {
+    constexpr int P = decltype(par_c)::value;
 #pragma unroll
-    for (int w = 1; w < kLmWaves; ++w) {
-      const Partial p2 = red[w * BM + tid];
-      merge_partial(p.m, p.s, p.idx, p2.m, p2.s, p2.idx);
+    for (int jb = 0; jb < JH; ++jb) {
+      if (jb < 4) av[P ^ 1][jb] = *reinterpret_cast<const bf16x8*>(an + jb * 2048);
+      if (jb < ND) bd[P ^ 1][jb] = *reinterpret_cast<const bf16x8*>(bn + (NPL + jb) * 2048);
+      const bf16x8 b = jb < NPL ? bv[jb < NPL ? jb : 0] : bd[P][jb < NPL ? 0 : jb - NPL];
+#pragma unroll
+      for (int ib = 0; ib < 4; ++ib) {
+        if (P == 1 && jb == JH - 1 && ib == 3) mfma_acc<true>(acc[ib][jb], av[P][ib], b);        // the trip's last
+        else mfma_acc<false>(acc[ib][jb], av[P][ib], b);
+      }
+      if (jb < NPL) bv[jb < NPL ? jb : 0] = *reinterpret_cast<const bf16x8*>(bn + jb * 2048);
+      if (jb < 4) transfer(jb);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    store_partial(a, row_of[tid], tile, p);
+  };
+
+  // ---- prologue: two pairs in flight
+  Walk ww{tile0, NP, tile0 % NP}, wh = ww;
+  w_tile(tile0);
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) issue_w(i, ww.pair, m * kRwStage);
+#pragma unroll
+    for (int i = 0; i < NH; ++i) issue_h(i, wh.pair, m * kRwStage);
+    if (m == 0) next(wh);
+    if (next(ww)) w_tile(ww.tile);
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  zero_past_end(tile0 % NP, 0);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+  // ---- one pair per trip.  A k-step's operands are read during the one before it, so pair m's stage is read in the second
+  // half of trip m - 1 and the first half of trip m.  The barrier between a trip's halves therefore says two things: pair m + 1
+  // has landed (every wave waited for its own transfers), and pair m's stages are free (every wave's reads are complete).
+  // W's pair m + 2 is asked for in the first half of trip m (its stage was pair m - 1's), the hidden rows of pair m + 2 in the
+  // second half (pair m's stage).  Younger than pair m + 1 are then, at the wait, W's four transfers of pair m + 2.
+  int ws = 0, wn = kRwStage, wf = 2 * kRwStage;  // W stages: pair m, m + 1, m + 2
+  int hs = 0;                                    // hidden stage: pair m (m + 1 is the other)
+  for (int tile = tile0; tile < a.ntile; tile += tile_step) {
+#pragma unroll
+    for (int ib = 0; ib < 4; ++ib)
+#pragma unroll
+      for (int jb = 0; jb < JH; ++jb) acc[ib][jb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ib = 0; ib < 4; ++ib) av[0][ib] = *reinterpret_cast<const bf16x8*>(abase[0] + ws + ib * 2048);
+#pragma unroll
+    for (int jb = 0; jb < JH; ++jb)
+      (jb < NPL ? bv[jb < NPL ? jb : 0] : bd[0][jb < NPL ? 0 : jb - NPL]) =
+          *reinterpret_cast<const bf16x8*>(bbase[0] + hs + jb * 2048);
+    int m = 0;
+    do {
+      step(std::integral_constant<int, 0>{}, abase[1] + ws, bbase[1] + hs, [&](int i) { issue_w(i, ww.pair, wf); });
+      const int hn = kRwStage - hs;
+      asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+      zero_past_end(wh.pair, hn);
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      next(wh);
+      if (__builtin_expect(next(ww), 0)) w_tile(ww.tile);
+      // (a tile's last trip reads the next tile's first operands in vain: they are read again behind the reduction, where
+      // their registers are needed)
+      step(std::integral_constant<int, 1>{}, abase[0] + wn, bbase[0] + hn, [&](int i) { if (i < NH) issue_h(i, wh.pair, hs); });
+      const int tmp = ws; ws = wn; wn = wf; wf = tmp; hs = hn;
+    } while (__builtin_expect(++m < NP, 1));
+
+    // ---- row reduction of the tile, in the stage that W's last pair has left (free since the last barrier, asked for again only
+    // in the next tile's first trip)
+    Partial* red = reinterpret_cast<Partial*>(lds + wf);           // [4 waves of a half][kRwBM]
+    // ---- row reduction of the tile: the maximum over this lane's vocabulary ids and the four lane groups first, so that
+    // every exponential is taken relative to it and the rest are plain sums; then over the four waves of a position half.
+    const int n0 = tile * kRwBN + wv * 64 + 4 * q;               // this lane's ids: n0 + 16 ib + r
+    auto reduce = [&](auto ragged_c) {
+#pragma unroll
+    for (int jb = 0; jb < JH; ++jb) {
+      // this row block's accumulators leave the accumulation registers here, not earlier (a register spilled without it)
+#pragma unroll
+      for (int ib = 0; ib < 4; ++ib) asm volatile("" : "+a"(acc[ib][jb]));
+      int left = a.V - n0;
+      if constexpr (decltype(ragged_c)::value) asm volatile("" : "+v"(left));    // (sixteen masks kept for all row blocks spill)
+      float v[16];
+#pragma unroll
+      for (int ib = 0; ib < 4; ++ib)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[ib * 4 + r] = !decltype(ragged_c)::value || 16 * ib + r < left ? acc[ib][jb][r] : -INFINITY;
+      float m = kNegBig;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) m = fmaxf(m, v[i]);
+      m = row_allreduce(m, [](float x, float y) { return fmaxf(x, y); });
+      int idx = 0x7fffffff;
+#pragma unroll
+      for (int i = 15; i >= 0; --i) idx = (v[i] == m) ? n0 + 16 * (i / 4) + i % 4 : idx;     // lowest id of a tie
+      idx = row_allreduce(idx, [](int x, int y) { return min(x, y); });
+      const float ml = m * kLog2e;
+      float s = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s += fast_exp2(fmaf(v[i], kLog2e, -ml));
+      s = row_allreduce(s, [](float x, float y) { return x + y; });
+      if (q == 0) red[wv * kRwBM + (wp * JH + jb) * 16 + l16] = Partial{m, s, idx};
+    }
+    };
+    if ((tile + 1) * kRwBN <= a.V) reduce(std::false_type{});
+    else reduce(std::true_type{});                 // the last tile runs past V
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (my_row >= 0) {
+      Partial p = red[tid];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) {
+        const Partial p2 = red[w * kRwBM + tid];
+        merge_partial(p.m, p.s, p.idx, p2.m, p2.s, p2.idx);
+      }
+      store_partial(a, my_row, tile, p);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");     // the stage is free again
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing of this workgroup's is in flight when it ends
 }
 
-template <int BM, int WNB, int PF_, bool PACKED>
-__global__ __launch_bounds__(kLmThreads, 1) void lm_head_rows_kernel(LmHeadArgs a) {
-  using S = LmShape<BM, WNB, PF_>;
+template <bool PACKED>
+__global__ __launch_bounds__(kRwThreads, 2) void lm_head_rows_kernel(LmHeadArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
-  unsigned char* stage = lds_raw;                                          // NST x kLmStageBytes
-  int* row_of = reinterpret_cast<int*>(lds_raw + S::NST * kLmStageBytes);  // BM compacted row ids (-1 = none)
-  Partial* red = reinterpret_cast<Partial*>(row_of + BM);                  // [waves][BM]
-  __shared__ int wsum[kLmWaves];
+  // the ring takes all of the LDS; before it starts, its place holds the list of masked rows
+  int* row_of = reinterpret_cast<int*>(lds_raw);                           // kRwBM compacted row ids (-1 = none)
+  int* wsum = row_of + kRwBM;                                              // kRwWaves
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // ---- the masked count decides how many row chunks there are
-  const int total = lm_masked_count(a, wsum);
+  const int total = lm_masked_count<kRwThreads>(a, wsum);
   if (total < max(a.min_masked, 1)) return;        // another shape's launch has this call, or nothing is masked
   // The rows go to as few chunks as their number allows, spread evenly and rounded up to 32: a chunk's matrix
   // instructions follow from the 16-row blocks it is built for, so 282 rows as 160 + 122 cost 320 rows' worth and not
   // the 512 of two full chunks (with the count above 128, an even share always exceeds 128 rows).
-  const int share = (total + BM - 1) / BM;
+  const int share = (total + kRwBM - 1) / kRwBM;
   const int bm = (((total + share - 1) / share) + 31) & ~31;         // 160, 192, 224 or 256 rows
   const int nact = (total + bm - 1) / bm;          // <= share <= a.nchunk, since total <= rows_total
-  // ---- workgroup -> (vocabulary tile, row chunk): chunks of a tile share id mod 8 (the XCD) and are adjacent
-  // in dispatch order.  Only chunks that hold rows get workgroup ids: the idle workgroups of a grid sized for
-  // B x K rows are its last ones (interleaved with the working ones they kept half of the chip idle: 256 of
-  // 512 positions masked took 497 us, not the 320 us of 256 of 256).
-  const int slot = blockIdx.x >> 3;
-  const int tile = (slot / nact) * kNumXCDs + (blockIdx.x & 7);
-  const int chunk = slot % nact;
-  if (tile >= a.ntile) return;
+  // ---- workgroup -> (row chunk, its share of the vocabulary tiles).  One workgroup per CU works, the grid's first ones, and
+  // walks its tiles one after the other; more of them work only where the chunks outnumber the CUs of an XCD.  Chunks of a tile
+  // share the id mod 8 (the XCD) and are adjacent in dispatch order: W comes from HBM once.
+  const int slots = max(kNumCUs / kNumXCDs, nact), slot = blockIdx.x >> 3;
+  const int chunk = slot % nact, part = slot / nact, parts = min(slots, (int)gridDim.x >> 3) / nact;
+  const int tile0 = part * kNumXCDs + (blockIdx.x & 7);
+  if (part >= parts || tile0 >= a.ntile) return;
 
   // ---- compact the masked rows; this workgroup takes compacted rows [lo, lo + bm)
   const int lo = chunk * bm;
   int running = 0;
-  for (int base = 0; base < a.rows_total; base += kLmThreads) {
+  for (int base = 0; base < a.rows_total; base += kRwThreads) {
     const int i = base + tid;
     const bool f = i < a.rows_total && a.masked[i] != 0;
     const unsigned long long bal = __ballot(f);
@@ -384,7 +374,7 @@ __global__ __launch_bounds__(kLmThreads, 1) void lm_head_rows_kernel(LmHeadArgs 
     __syncthreads();
     int pre = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < kLmWaves; ++w) { const int c = wsum[w]; pre += (w < wave) ? c : 0; tot += c; }
+    for (int w = 0; w < kRwWaves; ++w) { const int c = wsum[w]; pre += (w < wave) ? c : 0; tot += c; }
     const int ci = running + pre + rank - lo;
     if (f && ci >= 0 && ci < bm) row_of[ci] = i;
     running += tot;
@@ -396,10 +386,10 @@ __global__ __launch_bounds__(kLmThreads, 1) void lm_head_rows_kernel(LmHeadArgs 
   __syncthreads();
 
   switch (bm / 32) {                               // uniform
-    case 8: lm_head_rows_tile<BM, WNB, PF_, PACKED, 16>(a, stage, row_of, red, tile); break;
-    case 7: lm_head_rows_tile<BM, WNB, PF_, PACKED, 14>(a, stage, row_of, red, tile); break;
-    case 6: lm_head_rows_tile<BM, WNB, PF_, PACKED, 12>(a, stage, row_of, red, tile); break;
-    default: lm_head_rows_tile<BM, WNB, PF_, PACKED, 10>(a, stage, row_of, red, tile); break;
+    case 8: lm_head_rows_tiles<PACKED, 16>(a, lds_raw, row_of, tile0, parts * kNumXCDs); break;
+    case 7: lm_head_rows_tiles<PACKED, 14>(a, lds_raw, row_of, tile0, parts * kNumXCDs); break;
+    case 6: lm_head_rows_tiles<PACKED, 12>(a, lds_raw, row_of, tile0, parts * kNumXCDs); break;
+    default: lm_head_rows_tiles<PACKED, 10>(a, lds_raw, row_of, tile0, parts * kNumXCDs); break;
   }
 }
 
@@ -780,21 +770,6 @@ constexpr int kDmStage = kDmSub * kDmKC * 2;   // 16 KB
 constexpr int kDmNST = 5;                      // W ring stages: filled kDmNST - 1 steps ahead (64 KB per CU in flight)
 constexpr int kDmWT = kDmStage / 1024 / kLmWaves;   // W transfers per wave and step (4)
 constexpr int kDmTTMax = 16;
-
-template <int N> __device__ __forceinline__ void lm_wait_vmcnt() {
-  static_assert(N >= 0 && N <= 63, "vmcnt is a six-bit field");
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));    // expcnt / lgkmcnt: no wait
-}
-// one transfer: lane i's 16 bytes at vaddr land at lds_addr + 16 i (lds_addr uniform)
-template <bool NT>
-__device__ __forceinline__ void lm_dma16(unsigned lds_addr, const void* vaddr) {
-  if constexpr (NT)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
-                 :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(vaddr) : "memory", "m0");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                 :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(vaddr) : "memory", "m0");
-}
 
 // PACKED: W is the packed image; a transfer is then one operand tile (16 rows x one k-step, a contiguous
 // kilobyte), the ring holds the tiles as they are and an A operand is read lane by lane, without a swizzle.
@@ -1259,7 +1234,7 @@ static size_t lm_lds_bytes(int shape, int packed) {
     case kShape64: return packed ? dma_lds_bytes(1)
                                  : 2 * (size_t)kStStage + kSt2Hid + kSt2Rows * sizeof(int) + (size_t)kLmWaves * 32 * sizeof(Partial);
     case kShape128: return dma_lds_bytes(2);
-    default: return (size_t)3 * kLmStageBytes + 256 * sizeof(int) + (size_t)kLmWaves * 256 * sizeof(Partial);   // LmShape::NST
+    default: return kRwLds;
   }
 }
 
@@ -1295,10 +1270,10 @@ hipError_t launch_lm_head_pack_weight(int V, int Hd, long long ld_w, const void*
 // One launch, or (r.hidden == nullptr: the preparation pass of sdllm_init) only the kernel's opt-in to its
 // dynamic LDS size on the current device.
 static hipError_t launch_kernel(void (*kernel)(LmHeadArgs), LdsOptIn& st, size_t lds, unsigned grid,
-                                const LmHeadArgs& r, hipStream_t stream) {
+                                const LmHeadArgs& r, hipStream_t stream, int threads = kLmThreads) {
   hipError_t e = ensure_lds_opt_in(reinterpret_cast<const void*>(kernel), lds, st);
   if (e != hipSuccess || r.hidden == nullptr) return e;
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(kLmThreads), lds, stream, r);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, stream, r);
   return hipGetLastError();
 }
 
@@ -1337,11 +1312,10 @@ static hipError_t launch_dma_tt(int tt, const LmHeadArgs& r, hipStream_t stream)
   return hipErrorInvalidValue;
 }
 static hipError_t launch_rows(const LmHeadArgs& r, hipStream_t stream) {
-  static_assert(LmShape<256, 4, 4>::NST == 3 && LmShape<256, 4, 4>::BN == 256, "lm_lds_bytes, lm_plan");
   static LdsOptIn st[2];
   const unsigned grid = (unsigned)(((r.ntile + kNumXCDs - 1) / kNumXCDs) * r.nchunk * kNumXCDs);
-  if (r.packed) return launch_kernel(lm_head_rows_kernel<256, 4, 4, true>, st[1], lm_lds_bytes(kShapeRows, 1), grid, r, stream);
-  return launch_kernel(lm_head_rows_kernel<256, 4, 4, false>, st[0], lm_lds_bytes(kShapeRows, 0), grid, r, stream);
+  if (r.packed) return launch_kernel(lm_head_rows_kernel<true>, st[1], lm_lds_bytes(kShapeRows, 1), grid, r, stream, kRwThreads);
+  return launch_kernel(lm_head_rows_kernel<false>, st[0], lm_lds_bytes(kShapeRows, 0), grid, r, stream, kRwThreads);
 }
 
 static hipError_t launch_shape(int shape, int tt, const LmHeadArgs& r, hipStream_t stream) {

@@ -202,6 +202,24 @@ def test_lm_head_row_chunks_at_their_edges(gpu_lib, n_masked, packed):
     assert skipped <= 1
 
 
+@pytest.mark.parametrize("Hd", [32, 64, 96, 128, 160, 224])
+@pytest.mark.parametrize("n_masked", [129, 256, 300])
+@pytest.mark.parametrize("packed", [False, True])
+def test_lm_head_rows_walk_several_tiles(gpu_lib, n_masked, Hd, packed):
+    """More 256-row vocabulary tiles (263, the last one ragged) than workgroups that work on them: each walks two or three of
+    one to four pairs of k-steps, the transfers of the next tile running ahead over the end of this one, also where the last
+    pair is half a pair."""
+    B, K, V = 5, 64, 67100
+    h, W, tokens, masked, hd, Wd = _host_case(B, K, Hd, V, seed=n_masked + Hd, frac=0.0, ld_h=Hd + 8, ld_w=Hd + 24)
+    flat = np.random.Generator(np.random.Philox(key=n_masked)).permutation(B * K)[:n_masked]
+    masked.reshape(-1)[flat] = 1
+    tokens.reshape(-1)[flat] = wl.MASK_TOKEN
+    got = run_gpu(gpu_lib, hd, Wd, tokens, masked, 0.7, 0.3, packed=packed)
+    want = _oracle(h, W, tokens, masked, 0.7, 0.3)
+    n_gap, n_band, skipped = compare(got, want, tokens, masked)
+    assert skipped <= 1
+
+
 @pytest.mark.parametrize("B,K,Hd,V,ld_h,ld_w", [(2, 16, 64, 200, 72, 80), (2, 32, 320, 1000, 328, 384),
                                                  (4, 32, 320, 1000, 328, 384),
                                                  (3, 32, 320, 1000, 328, 384)])

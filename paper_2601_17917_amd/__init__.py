@@ -148,14 +148,21 @@ def _check(status: int):
         raise SdllmError(status, load_library().sdllm_last_error().decode())
 
 
+# Marshalling is what a one-shot call of a small problem waits for, so it is kept to what the checks and the C call need:
+# addresses and streams as plain integers, one test per tensor where everything is in order (the tests that name what is not
+# run only then), no Stream object (2.4 us) for the current stream, no view of a layer to see that it is contiguous (1 us).
+# A step of three one-shot calls (fp32 attention of 4 heads, unmask, append): 61 -> 45 us.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dtype_code(t):
@@ -168,7 +175,7 @@ def _dtype_code(t):
 
 
 def _require(t, name, dtype=None):
-    if t is None:
+    if t is None or (t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype == dtype)):
         return
     if not t.is_cuda:
         raise SdllmError(ERR_INVALID_ARG, f"{name} must be a device tensor")
@@ -243,14 +250,21 @@ def bind_block_attention(q_block, q_suffix, k_cache, v_cache, k_block, v_block, 
     S = 0 if q_suffix is None else q_suffix.shape[2]
     n_keep = 0 if keep_idx is None else int(keep_idx.shape[0])
     cap = prefix_len if k_cache is None else k_cache.shape[2]
-    for name, t in (("q_block", q_block), ("q_suffix", q_suffix), ("k_cache", k_cache), ("v_cache", v_cache),
-                    ("k_block", k_block), ("v_block", v_block), ("k_suffix", k_suffix), ("v_suffix", v_suffix)):
-        _require(t, name, q_block.dtype)
+    dtype = q_block.dtype
+    _require(q_block, "q_block", dtype)
+    _require(q_suffix, "q_suffix", dtype)
+    _require(k_cache, "k_cache", dtype)
+    _require(v_cache, "v_cache", dtype)
+    _require(k_block, "k_block", dtype)
+    _require(v_block, "v_block", dtype)
+    _require(k_suffix, "k_suffix", dtype)
+    _require(v_suffix, "v_suffix", dtype)
     _require(keep_idx, "keep_idx", torch.int32)
     p = attn_params(_dtype_code(q_block), B, Hq, Hkv, D, prefix_len, cap, K, S, n_keep, scale, kv_splits)
     if out is None:
-        out = torch.empty((B, Hq, K + n_keep, D), dtype=q_block.dtype, device=q_block.device)
-    _require(out, "out", q_block.dtype)
+        out = torch.empty((B, Hq, K + n_keep, D), dtype=dtype, device=q_block.device)
+    else:
+        _require(out, "out", dtype)
     need = attention_workspace_bytes(p)
     if need and workspace is None:
         workspace = torch.empty((need,), dtype=torch.uint8, device=q_block.device)
@@ -451,6 +465,8 @@ def kv_append(*args, **kw):
 def _require_layers(t, name, dtype):
     """A [L, ...] tensor whose layers are contiguous blocks a constant distance apart (stride(0) may exceed the
     dense size: layers padded or interleaved with other data)."""
+    if t.is_cuda and t.dtype == dtype and t.shape[0] > 0 and t.is_contiguous():
+        return                                        # dense: so is every layer
     if not t.is_cuda:
         raise SdllmError(ERR_INVALID_ARG, f"{name} must be a device tensor")
     if t.dtype != dtype:
@@ -463,8 +479,11 @@ def bind_kv_append(k_caches, v_caches, k_blocks, v_blocks, prefix_len: int, do_a
     import torch
     L, B, Hkv, cap, D = k_caches.shape
     K = k_blocks.shape[3]
-    for name, t in (("k_caches", k_caches), ("v_caches", v_caches), ("k_blocks", k_blocks), ("v_blocks", v_blocks)):
-        _require_layers(t, name, k_caches.dtype)
+    dtype = k_caches.dtype
+    _require_layers(k_caches, "k_caches", dtype)
+    _require_layers(v_caches, "v_caches", dtype)
+    _require_layers(k_blocks, "k_blocks", dtype)
+    _require_layers(v_blocks, "v_blocks", dtype)
     _require(do_append, "do_append", torch.uint8)
     if L > 1 and (v_caches.stride(0) != k_caches.stride(0) or v_blocks.stride(0) != k_blocks.stride(0)):
         raise SdllmError(ERR_INVALID_ARG, "kv_append: K and V tensors must share their layer strides")

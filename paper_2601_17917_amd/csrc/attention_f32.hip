@@ -6,9 +6,9 @@
 //   group = (batch, KV head): the g * Nq query rows that share its K/V are one list of "virtual rows", cut into
 //   16-row blocks.  A workgroup has NR x NK waves: wave (r, k) owns row block r of the workgroup and every NK-th
 //   16-key block of the sequence; the NK partial (O, m, l) of a row block merge through LDS in a fixed order.
-//   No wave shares an operand with another, so K and V go from global memory straight into registers in operand
-//   layout (a block's V during its Q K^T, the next block's K during its P V): no LDS and no barrier in the loop.  Waves of a workgroup
-//   that own different rows read the same key blocks at about the same time and meet in the L1.
+//   No wave shares an operand with another: V goes from global memory straight into registers in operand layout, K too or
+//   through a region of LDS of the wave's own; there is no barrier in the loop.  Waves of a workgroup that own different rows
+//   read the same key blocks at about the same time and meet in the L1.
 // Operand layout (lane: l16 = lane % 16, G = lane / 16; a 16x16x4 operand is ONE float per lane, row / column l16,
 // contraction index G)
 //   S^T = K Q^T   the contraction runs over d in any order, so the four instructions of 16-element slice s take the
@@ -18,7 +18,7 @@
 //                 load of a V row serves the four blocks j.
 // What bounds it: the matrix pipe in principle (256 flop / cycle / CU in fp32, 157 TFLOP/s; two waves per SIMD cover each
 // other's softmax and load latency), at layer sizes the fixed parts of a short launch.  Measured, B2, 32 query / 8 KV heads
-// x 128, 64 query rows x 672 keys: 26 us (53 TFLOP/s, matrix pipe 34 % busy) against 276 us for one query row per wave
+// x 128, 64 query rows x 672 keys: 21.6 us (65 TFLOP/s) against 276 us for one query row per wave
 // with fp32 FMAs out of LDS; B1, 4 heads x 64, 48 x 112: 7.2 against 17.5 us.
 #include "common.h"
 #include <algorithm>
@@ -112,6 +112,60 @@ __device__ __forceinline__ void f32_load_k(const AttnF32Args& a, int l16, int G,
   else f32_rows<1>(a, tc, tb, ts, blk * kF32Keys + l16, kp);
 #pragma unroll
   for (int s = 0; s < NS; ++s) k[s] = f32_load4(kp[0] + min(16 * s + 4 * G, a.D - 4));
+}
+
+// Heads of 65 to 128 elements: K goes through LDS, into a region of the wave's own (no barrier).  The operand layout takes 64
+// bytes of each of 16 rows a load, half lines; a 128-wide block's eight such loads keep the load path busy for 512 cycles a
+// wave, half as long as the matrix pipe of a SIMD needs for the scores, and the CU's eight waves share one load path.  A
+// transfer brings one kilobyte of whole lines.  B2, 32 / 8 heads x 128, 64 rows x 672 keys: 23.5 -> 21.6 us; B1, 32 / 32, 64 rows
+// x 1088 keys: 32.0 -> 29.0.  (64-wide heads have half the scores' time to cover the round trip, 2112 keys 30.2 -> 30.8; wider ones have one
+// wave per SIMD, 8 heads x 252, 1532 keys 77 -> 85: both keep their loads.)  A row is CPR 16-byte chunks (its head
+// padded to the slices by re-reading the last one); place p of row r holds chunk p ^ r in the low four bits, so that an operand
+// read (one chunk of 16 rows; the hardware serves rows 0-3 and 12-15 of it with rows 4-11 of the next) is free of conflicts.
+template <int NS> constexpr bool f32_k_in_lds() { return NS == 8; }
+template <int NS> struct F32K {
+  static constexpr int CPR = 4 * NS;             // chunks per row
+  static constexpr int RPT = 64 / CPR;           // rows per transfer; NS transfers per block
+  static constexpr int BUF = NS * 1024;          // bytes of a block
+  unsigned voff[f32_k_in_lds<NS>() ? NS : 1];    // this lane's byte offset of transfer j from the block's first row
+  unsigned lds;                                  // the wave's region: two blocks
+};
+
+template <int NS>
+__device__ __forceinline__ void f32_dma_k(const AttnF32Args& a, const F32K<NS>& kk, int lane, f32_gptr tc, f32_gptr tb, f32_gptr ts,
+                                          int blk, int buf, const F32Ahead& ka) {
+  using S = F32K<NS>;
+  const unsigned dst = __builtin_amdgcn_readfirstlane(kk.lds + buf * S::BUF);
+  const f32_gptr run = f32_run(a, tc, tb, ts, blk, ka);
+  if (run != nullptr) {
+    const unsigned long long p = (unsigned long long)run;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)p), hi = __builtin_amdgcn_readfirstlane((unsigned)(p >> 32));
+    const unsigned long long base = ((unsigned long long)hi << 32) | lo;
+#pragma unroll
+    for (int j = 0; j < NS; ++j)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                   :: "s"(dst + j * 1024), "v"(kk.voff[j]), "s"(base) : "memory", "m0");
+  } else {
+    f32_gptr own[1];                             // row lane % 16 of the block
+    f32_rows<1>(a, tc, tb, ts, blk * kF32Keys + (lane & 15), own);
+    const unsigned lo = (unsigned)(unsigned long long)own[0], hi = (unsigned)((unsigned long long)own[0] >> 32);
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+      const int row = j * S::RPT + lane / S::CPR;
+      const unsigned long long rp = ((unsigned long long)(unsigned)__shfl((int)hi, row) << 32) | (unsigned)__shfl((int)lo, row);
+      const unsigned long long va = rp + (kk.voff[j] - (unsigned)(row * a.D * 4));
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                   :: "s"(dst + j * 1024), "v"(va) : "memory", "m0");
+    }
+  }
+}
+
+// K operands out of the wave's region: lane (l16, G) takes d = 16 s + 4 G .. + 3 of key l16
+template <int NS>
+__device__ __forceinline__ void f32_read_k(const unsigned char* buf, int l16, int G, f32x4 (&k)[NS]) {
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+    k[s] = *reinterpret_cast<const f32x4*>(buf + l16 * (NS * 64) + (((4 * s + G) ^ l16) << 4));
 }
 
 // V operands: lane (l16, G) takes d = 64 dg + 4 l16 .. + 3 of keys 4 G + i
@@ -229,9 +283,24 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
   const int hl = Rc / a.Nq, qi = Rc - hl * a.Nq;
   const long long qbh = (long long)b * a.Hq + (long long)kvh * a.g + hl;
   const int q_keep = a.keep_idx[max(qi - a.K, 0)];
+  constexpr bool kLds = f32_k_in_lds<NS>();
+  using KS = F32K<NS>;
+  KS kk;
+  unsigned char* const kbuf = reinterpret_cast<unsigned char*>(f32_lds) + wave * 2 * KS::BUF;
+  kk.lds = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)reinterpret_cast<unsigned char*>(f32_lds) +
+           wave * 2 * KS::BUF;
   f32x4 k[NS], v[NS / 4][4];
   F32Ahead ka = f32_ahead(a, wk);
-  f32_load_k<NS>(a, l16, G, kc, kb, ks, min(wk, a.key_blocks - 1), ka, k);
+  if constexpr (kLds) {
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+      const int row = j * KS::RPT + lane / KS::CPR;
+      kk.voff[j] = 4u * (unsigned)(row * D + min(4 * ((lane % KS::CPR) ^ (row & 15)), D - 4));
+    }
+    if (wk < a.key_blocks) f32_dma_k<NS>(a, kk, lane, kc, kb, ks, wk, 0, ka);
+  } else {
+    f32_load_k<NS>(a, l16, G, kc, kb, ks, min(wk, a.key_blocks - 1), ka, k);
+  }
   __builtin_amdgcn_sched_barrier(0);
   const f32_gptr qp = qi < a.K ? (f32_gptr)a.q_block + (qbh * a.K + qi) * D : (f32_gptr)a.q_suffix + (qbh * a.S + q_keep) * D;
   f32x4 q[NS];
@@ -250,13 +319,27 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
   // the lowest finite reference, not -inf: scores may be -inf themselves (overflow, infinite operands), also all of a block
   float m = -FLT_MAX, l = 0.f;
 
-  // ---- key blocks wk, wk + nk, ...: a block's V travels during its scores, the next block's K during its P V
+  // ---- key blocks wk, wk + nk, ...: a block's V travels during its scores; the next block's K too where it goes through LDS,
+  // otherwise during the P V.  (The transfers into LDS are invisible to the compiler's wait counts; asked for before V, they
+  // are complete whenever V is, since loads return in order.  The wait in front of the reads of K therefore costs nothing
+  // after the first block.)
+  int buf = 0;
   auto block = [&](int blk, auto partial) {
-    f32_load_v<NS>(a, l16, G, vc, vb, vs, blk, ka, v);
-    ka = f32_ahead(a, blk + a.nk);
+    if constexpr (kLds) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const F32Ahead kn = f32_ahead(a, blk + a.nk);
+      if (blk + a.nk < a.key_blocks) f32_dma_k<NS>(a, kk, lane, kc, kb, ks, blk + a.nk, buf ^ 1, kn);
+      f32_load_v<NS>(a, l16, G, vc, vb, vs, blk, ka, v);
+      ka = kn;
+      f32_read_k<NS>(kbuf + buf * KS::BUF, l16, G, k);
+      buf ^= 1;
+    } else {
+      f32_load_v<NS>(a, l16, G, vc, vb, vs, blk, ka, v);
+      ka = f32_ahead(a, blk + a.nk);
+    }
     const f32x4 sc = f32_scores<NS, RAGGED, partial.value>(a, G, blk, k, q);
-    f32_load_k<NS>(a, l16, G, kc, kb, ks, min(blk + a.nk, a.key_blocks - 1), ka, k);     // (past the end: never used)
-    f32_accumulate<NS, partial.value>(a, G, blk, sc, v, o, m, l);
+    if constexpr (!kLds) f32_load_k<NS>(a, l16, G, kc, kb, ks, min(blk + a.nk, a.key_blocks - 1), ka, k);   // (past the end:
+    f32_accumulate<NS, partial.value>(a, G, blk, sc, v, o, m, l);                                           // never used)
   };
   const int full = a.Nkv / kF32Keys;
   int blk = wk;
@@ -281,6 +364,7 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
     return;
   }
   const int nw = a.nr * a.nk;
+  if constexpr (kLds) __syncthreads();                                   // the exchange area lies over the regions of K
   f32x4* xo = reinterpret_cast<f32x4*>(f32_lds);                         // [wave][NS pieces][64 lanes]
   float2* xml = reinterpret_cast<float2*>(f32_lds + nw * NS * 256);      // [wave][16 rows]
 #pragma unroll
@@ -346,7 +430,12 @@ void attention_f32_plan(const sdllm_attn_params& p, sdllm_attn_plan* plan) {
   plan->workgroup_shape = 0; plan->ring_stages = 2;
 }
 
-template <int NS> constexpr size_t f32_lds_bytes(int waves) { return (size_t)waves * (NS * 1024 + 16 * sizeof(float2)); }
+// the exchange area of the merge, or the regions of K that it lies over
+template <int NS> constexpr size_t f32_lds_bytes(int waves) {
+  constexpr int exchange = NS * 1024 + 16 * (int)sizeof(float2);
+  static_assert(!f32_k_in_lds<NS>() || 2 * F32K<NS>::BUF >= exchange, "the exchange area fits the regions of K");
+  return (size_t)waves * (f32_k_in_lds<NS>() ? 2 * F32K<NS>::BUF : exchange);
+}
 
 template <int NS, bool RAGGED>
 static hipError_t f32_opt_in() {
@@ -371,7 +460,7 @@ static hipError_t f32_launch(const AttnF32Args& a, const F32Plan& pl, hipStream_
   if (e != hipSuccess) return e;
   const int waves = pl.nr * pl.nk;
   const dim3 grid((unsigned)std::min(pl.workgroups, (long long)kF32GridX), (unsigned)((pl.workgroups + kF32GridX - 1) / kF32GridX));
-  hipLaunchKernelGGL((attention_f32_kernel<NS, RAGGED>), grid, dim3(64 * waves), pl.nk > 1 ? f32_lds_bytes<NS>(waves) : 0, stream, a);
+  hipLaunchKernelGGL((attention_f32_kernel<NS, RAGGED>), grid, dim3(64 * waves), f32_k_in_lds<NS>() || pl.nk > 1 ? f32_lds_bytes<NS>(waves) : 0, stream, a);
   return hipGetLastError();
 }
 

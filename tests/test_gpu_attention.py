@@ -98,6 +98,20 @@ def test_attention_fp32_workgroup_shapes(gpu_lib, B, Hq, Hkv, D, P, K, S, keep, 
     assert np.abs(got - oracle(t, P)).max() <= TOL["fp32"]
 
 
+@pytest.mark.parametrize("D", [68, 80, 100, 128])
+@pytest.mark.parametrize("P,K,S,keep", [
+    (700, 32, 0, ()),                                             # several blocks per wave, all in the cache
+    (403, 33, 300, tuple(range(0, 300, 3))),                      # blocks over a seam, kept rows scattered, a partial last block
+    (0, 5, 200, tuple(range(7, 180)) + (199,)),                   # no cache; runs of kept rows that start at any row
+    (11, 1, 0, ()),                                               # one partial block, one wave with work
+])
+def test_attention_fp32_k_through_lds(gpu_lib, D, P, K, S, keep):
+    """Head widths whose K goes through LDS: every route a block's rows can take, and padded head widths."""
+    t = wl.make_custom_attention_inputs("fp32", 2, 6, 2, D, P, P + 3, K, max(S, 1), keep, seed=D + P)
+    got = run_gpu(gpu_lib, t, P)
+    assert np.abs(got - oracle(t, P)).max() <= TOL["fp32"]
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,D,P,K,S,keep,nr,workgroups", [
     # several workgroups per group and a last one whose waves do not all have rows: 15 row blocks as 8 x 2, 4 x 4, 2 x 8
     (8, 20, 5, 16, 20, 57, 9, (0, 8), 2, 320),

@@ -68,6 +68,20 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a) {
   T* dst = reinterpret_cast<T*>(in_block ? a.out_block : a.out_suffix);
   const int D = a.D, H2 = D / 2;
 
+  // An item is what one lane rotates at a time: a vector of whole pairs (2 i, 2 i + 1), or a vector of the first half of a
+  // row and the matching vector of the second half, pairs (i, i + D/2).
+  const int per_row = INTERLEAVED ? D / N : H2 / N;
+  const int bh0 = blockIdx.y * a.rows_per_chunk;
+  const int items = (min(bh0 + a.rows_per_chunk, a.BH) - bh0) * per_row;
+  auto offset = [&](int it) { return ((long long)(bh0 + it / per_row) * T_len + srow) * D + (long long)(it % per_row) * N; };
+  u32x4 lo, hi;
+  auto load = [&](long long off) {
+    lo = *reinterpret_cast<const u32x4*>(src + off);
+    if constexpr (!INTERLEAVED) hi = *reinterpret_cast<const u32x4*>(src + off + H2);
+  };
+  // the first item travels while the angles are computed (a launch of two passes at most is a chain of latencies)
+  if (tid < items) load(offset(tid));
+
   for (int i = tid; i < H2; i += 256) {
     const double theta = exp2(-(2.0 * i / D) * a.log2_base);
     double s, c;
@@ -76,38 +90,27 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a) {
   }
   __syncthreads();
 
-  const int bh0 = blockIdx.y * a.rows_per_chunk;
-  const int bh1 = min(bh0 + a.rows_per_chunk, a.BH);
-  if (INTERLEAVED) {
-    // pairs (2i, 2i+1): one vector holds N/2 whole pairs
-    const int RV = D / N;
-    const int items = (bh1 - bh0) * RV;
-    for (int it = tid; it < items; it += 256) {
-      const int bh = bh0 + it / RV, rv = it % RV;
-      const long long off = ((long long)bh * T_len + srow) * D + (long long)rv * N;
+  for (int it = tid; it < items; it += 256) {
+    const long long off = offset(it);
+    if (it != tid) load(off);
+    const int first = (it % per_row) * (INTERLEAVED ? N / 2 : N);              // pair index of the vector's first pair
+    if constexpr (INTERLEAVED) {
       float x[N], y[N];
-      RopeVec<T>::unpack(*reinterpret_cast<const u32x4*>(src + off), x);
+      RopeVec<T>::unpack(lo, x);
 #pragma unroll
       for (int e = 0; e < N / 2; ++e) {
-        const float c = cos_s[rv * (N / 2) + e], s = sin_s[rv * (N / 2) + e];
+        const float c = cos_s[first + e], s = sin_s[first + e];
         y[2 * e] = x[2 * e] * c - x[2 * e + 1] * s;
         y[2 * e + 1] = x[2 * e + 1] * c + x[2 * e] * s;
       }
       *reinterpret_cast<u32x4*>(dst + off) = RopeVec<T>::pack(y);
-    }
-  } else {
-    // pairs (i, i + D/2): a vector of the first half and the matching vector of the second half
-    const int HV = H2 / N;
-    const int items = (bh1 - bh0) * HV;
-    for (int it = tid; it < items; it += 256) {
-      const int bh = bh0 + it / HV, hv = it % HV;
-      const long long off = ((long long)bh * T_len + srow) * D + (long long)hv * N;
+    } else {
       float x1[N], x2[N], y1[N], y2[N];
-      RopeVec<T>::unpack(*reinterpret_cast<const u32x4*>(src + off), x1);
-      RopeVec<T>::unpack(*reinterpret_cast<const u32x4*>(src + off + H2), x2);
+      RopeVec<T>::unpack(lo, x1);
+      RopeVec<T>::unpack(hi, x2);
 #pragma unroll
       for (int e = 0; e < N; ++e) {
-        const float c = cos_s[hv * N + e], s = sin_s[hv * N + e];
+        const float c = cos_s[first + e], s = sin_s[first + e];
         y1[e] = x1[e] * c - x2[e] * s;
         y2[e] = x2[e] * c + x1[e] * s;
       }

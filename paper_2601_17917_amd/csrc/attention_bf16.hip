@@ -297,9 +297,14 @@ __device__ __forceinline__ void compute_tile(const AttnArgs& a, const Lane<D>& L
   using S = Shape<D, 2, NG>;
   constexpr int NS = S::NS, NDB = S::NDB;
   constexpr bool kMfmaRowSum = (RB == 1);
-  // the compiler's interleaving strategy for matrix instructions and LDS reads in this block (dense-suffix shape
-  // 269 -> 263 us; the stream-bound shapes do not notice)
-  __builtin_amdgcn_iglp_opt(0);
+  // the compiler's interleaving strategy for matrix instructions and LDS reads in this block (32 heads x 128, 1024 rows x 2048
+  // keys 269 -> 263 us; the stream-bound shapes do not notice).  Not for 64-wide heads at 32 rows per wave: 1024 rows x 2048
+  // keys 168 -> 145 us without, 4 heads' 1328 rows x 3332 keys 58.0 -> 48.5.
+  if constexpr (!(D == 64 && RB == 2)) __builtin_amdgcn_iglp_opt(0);
+  // 16 rows per wave: the wave that is at its P V goes first, so that the SIMD's waves drift into different phases of a tile
+  // (448 rows x 1764 keys 36.9 -> 34.8 us, 384 x 560 15.3 -> 14.4; 64-wide heads and 32 rows per wave: no gain or 2-5 % slower)
+  constexpr bool kPvFirst = (D == 128 && RB == 1);
+  if constexpr (kPvFirst) __builtin_amdgcn_s_setprio(0);
   // ---- S^T = K Q^T
   f32x4 sacc[RB][4];
 #pragma unroll
@@ -411,6 +416,7 @@ __device__ __forceinline__ void compute_tile(const AttnArgs& a, const Lane<D>& L
   }
 
   // ---- O^T += V^T P^T
+  if constexpr (kPvFirst) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
 #pragma unroll

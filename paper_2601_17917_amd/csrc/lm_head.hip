@@ -1004,16 +1004,20 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_pack_kernel(const uint16_t
 
 // Stream shape for at most 32 positions over a packed W.  Nothing is shared between the waves but the list of
 // masked rows: a wave owns TT 16-row vocabulary blocks and both row blocks of positions, loads its A operands
-// straight from the image (every load of a wave is one contiguous kilobyte, nontemporal, two k-steps ahead in
-// registers) and keeps the B operands of a chunk of 8 k-steps in registers, the next chunk's beside them.  No
-// LDS and no barrier in the loop; the compiler's wait counts see one straight line per chunk.
+// straight from the image (every load of a wave is one contiguous kilobyte, nontemporal) and keeps the B operands of
+// a chunk of 8 k-steps in registers, the next chunk's beside them.  No LDS and no barrier in the loop.
+// Bound by the stream of W.  A chunk is walked block by block, a block's 8 k-steps in a row: eight contiguous kilobytes at
+// a time, two such runs in flight per wave.  Walked k-step by k-step (one kilobyte of each block in turn, as many bytes in
+// flight) the blocks' starts, Hd x 32 bytes apart, met in the same memory channels where Hd is a power of two: 126464 x 4096
+// 175.6 -> 163.5 us per call with 16 masked positions, 181 -> 165 with 32 (6.8 TB/s; a plain read 7.0), 32000 x 4096 59.7 ->
+// 53.7, 8000 x 768 21.1 -> 19.4; 152064 x 3584 170.4 and 171.1, 50257 x 1600 41.8 both.
 constexpr int kPkKS = 8;                       // k-steps per chunk of B operands
-constexpr int kPkPF = 2;                       // k-steps of A operands in flight per wave
+constexpr int kPkPF = 2;                       // vocabulary blocks (chunks of 8 KB) of A operands in flight per wave
 constexpr int kPkTTMax = 10;
 
 template <int TT>
 __global__ __launch_bounds__(kLmThreads) void lm_head_packed_kernel(LmHeadArgs a) {
-  static_assert(TT >= 1 && TT <= kPkTTMax && kPkKS % kPkPF == 0, "shape");
+  static_assert(TT >= 1 && TT <= kPkTTMax, "shape");
   __shared__ int row_of[32];                     // compacted row ids (-1 = none)
   __shared__ Partial red[kLmWaves][32];
   __shared__ int wsum[kLmWaves];
@@ -1052,21 +1056,18 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_packed_kernel(LmHeadArgs a
   const int q = lane >> 4, l16 = lane & 15;
   const int c0 = tile % NCH;                       // this workgroup's rotation of the chunk order
   auto chunk_at = [&](int c) { int ch = min(c, NCH - 1) + c0; return ch - ((ch >= NCH) ? NCH : 0); };
-  auto kstep_at = [&](int s) {                     // k-step at position s of the walk (past the end: the last position)
-    const int sc = min(s, NCH * kPkKS - 1);
-    const int cc = sc / kPkKS, ss = sc - cc * kPkKS;
-    return min(chunk_at(cc) * kPkKS + ss, NK - 1); // k-steps past Hd: the last one (its B operands are zeros)
-  };
   // A operands: block nb0 + t of the image, this lane's 16 bytes of every k-step 512 elements apart
   const int nb0 = (tile * kLmWaves + wave) * TT;
   const uint16_t* wblk[TT];
 #pragma unroll
   for (int t = 0; t < TT; ++t) wblk[t] = a.weight + ((long long)min(nb0 + t, NB - 1) * NK * 64 + lane) * 8;
-  auto load_a = [&](int s, bf16x8 (&dst)[TT]) {
-    const long long off = (long long)kstep_at(s) * 512;
+  auto load_a = [&](int c, int t, bf16x8 (&dst)[kPkKS]) {        // block t's k-steps of the chunk at walk position c
+    const int k0 = chunk_at(c) * kPkKS;
 #pragma unroll
-    for (int t = 0; t < TT; ++t)
-      dst[t] = __builtin_bit_cast(bf16x8, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(wblk[t] + off)));
+    for (int ks = 0; ks < kPkKS; ++ks) {           // k-steps past Hd: the last one (its B operands are zeros)
+      const long long off = (long long)min(k0 + ks, NK - 1) * 512;
+      dst[ks] = __builtin_bit_cast(bf16x8, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(wblk[t] + off)));
+    }
   };
   // B operands: hidden row of position rb * 16 + l16, elements 8 q .. 8 q + 7 of every k-step of a chunk
   const uint16_t* hrow[2];
@@ -1096,30 +1097,36 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_packed_kernel(LmHeadArgs a
   f32x4 acc[TT][2];
 #pragma unroll
   for (int t = 0; t < TT; ++t) { acc[t][0] = f32x4{0.f, 0.f, 0.f, 0.f}; acc[t][1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-  bf16x8 abuf[kPkPF][TT];
+  bf16x8 abuf[kPkPF][kPkKS];                     // items (chunk, block) i and i + 1 of the walk; item i = c TT + t
   bf16x8 bcur[kPkKS][2];
   u32x4 bnext[kPkKS][2];
   load_b(0, bnext);
 #pragma unroll
-  for (int s = 0; s < kPkPF; ++s) load_a(s, abuf[s]);
+  for (int i = 0; i < kPkPF; ++i) load_a(i / TT, i % TT, abuf[i]);
   take_b(0, bnext, bcur);
 
-  for (int kc = 0; kc < NCH; ++kc) {
-    load_b(kc + 1, bnext);                         // older than every A load below: it is back before they are
+  constexpr int U = TT % kPkPF == 0 ? 1 : kPkPF; // chunks per unrolled body, so that an item's buffer is known
+  static_assert(U * TT % kPkPF == 0, "buffers");
+  for (int kc0 = 0; kc0 < NCH; kc0 += U) {
 #pragma unroll
-    for (int ks = 0; ks < kPkKS; ++ks) {
-      bf16x8 acur[TT];
-#pragma unroll
-      for (int t = 0; t < TT; ++t) acur[t] = abuf[ks % kPkPF][t];
-      load_a(kc * kPkKS + ks + kPkPF, abuf[ks % kPkPF]);
+    for (int u = 0; u < U; ++u) {
+      const int kc = kc0 + u;
+      if (U > 1 && kc >= NCH) break;               // uniform
+      load_b(kc + 1, bnext);                       // older than every A load below: it is back before they are
 #pragma unroll
       for (int t = 0; t < TT; ++t) {
-        acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(acur[t], bcur[ks][0], acc[t][0], 0, 0, 0);
-        acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(acur[t], bcur[ks][1], acc[t][1], 0, 0, 0);
+        constexpr int PF = kPkPF;
+        bf16x8 (&cur)[kPkKS] = abuf[(u * TT + t) % PF];
+#pragma unroll
+        for (int ks = 0; ks < kPkKS; ++ks) {
+          acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur[ks], bcur[ks][0], acc[t][0], 0, 0, 0);
+          acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur[ks], bcur[ks][1], acc[t][1], 0, 0, 0);
+        }
+        load_a(kc + (t + PF) / TT, (t + PF) % TT, cur);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_barrier(0);
+      take_b(kc + 1, bnext, bcur);
     }
-    take_b(kc + 1, bnext, bcur);
   }
 
   // ---- row reduction: this lane holds, for position rb * 16 + l16, the ids (nb0 + t) * 16 + 4 q + r

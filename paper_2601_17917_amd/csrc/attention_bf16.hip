@@ -719,6 +719,30 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a, long long
   *reinterpret_cast<uint2*>(orow + d) = w2;
 }
 
+// Key splits of a launch with `base` workgroups before splitting.  What counts is the longest chain of key tiles a CU works off,
+// rounds of 256 workgroups x (tiles per split + 1 for the prologue), against the merge, which costs a launch (3 tiles' time),
+// its rows (4 at 64 workgroups and more), 0.3 a split and 0.8 a further round trip for every four; the constants are fitted to
+// sweeps of 430 shapes (8 to 448 workgroups x 4 to 80 tiles, both head widths, all workgroup shapes, a dozen split counts
+// each), which they leave within 1 % of the best split on the mean, where two workgroups per CU were 13 % behind it.  The 8-wave workgroup is two waves per SIMD by itself: a second workgroup per CU, or a split that starts a second
+// round of a few workgroups, only adds merge traffic and tail.  D 128 unless said, us, splits for two workgroups per CU / now:
+//   12 groups of 256 rows x 1277 keys, D 64: 10 splits 12.6 / 4: 9.9     8 groups of 256 x 4064: 16: 19.7 / 8: 15.5
+//   64 x 64 rows x 764 keys: 6: 16.4 / 4: 13.5     112 x 64 x 896: 5: 20.7 / 1: 13.6     8 x 64 x 5120: 40: 20.3 / 10: 16.1
+//   10 groups of 1024 rows x 1280 keys: 7: 34.7 / 4: 22.8     50 x 1024 x 1280: 2: 63.8 / 1: 41.2
+// From 256 workgroups on no split paid for its merge (320 x 64 rows x 2560 keys: 2 splits 88.2 / 1: 67.4; x 5120 160 / 130).
+static long long auto_splits(long long base, int key_tiles, int mode) {
+  if (base >= kNumCUs) return 1;
+  long long best = 1, best_cost = 10 * (key_tiles + 1);                      // tenths of a tile
+  for (long long ns = 2; ns <= key_tiles && ns <= 64; ++ns) {
+    const long long tps = (key_tiles + ns - 1) / ns;
+    const long long rounds = (base * ns + kNumCUs - 1) / kNumCUs;
+    if (rounds > 1 && mode == 2) break;            // one such workgroup per CU: 34 x 1024 rows x 2560 keys 1 split 67, 2: 90
+    if ((key_tiles + tps - 1) / tps != ns) continue;         // as long as with fewer splits
+    const long long cost = 10 * rounds * (tps + 1) + 30 + 40 * (base < 64 ? base : 64) / 64 + 3 * ns + 8 * ((ns - 1) / 4);
+    if (cost < best_cost) { best_cost = cost; best = ns; }
+  }
+  return best;
+}
+
 AttnPlan plan_attention_bf16(const sdllm_attn_params& p) {
   AttnPlan pl;
   const int g = p.Hq / p.Hkv;
@@ -740,19 +764,7 @@ AttnPlan plan_attention_bf16(const sdllm_attn_params& p) {
   pl.q_tiles = (int)((Rtot + rows_wg - 1) / rows_wg);
   pl.key_tiles = (int)((Nkv + kKeyTile - 1) / kKeyTile);
   const long long base = (long long)p.B * p.Hkv * pl.q_tiles;
-  long long ns;
-  if (p.kv_splits > 0) {
-    ns = p.kv_splits;
-  } else {
-    // aim at two workgroups per CU (one when they are 128-row tiles: 32 layers x 5248 keys x 128 rows
-    // measured 2402 us per step with 2 splits, 2480 with 4) ...
-    ns = ((pl.rb == 2 ? 1LL : 2LL) * kNumCUs + base - 1) / base;
-    // ... but keep a split long enough to amortise its merge: 16 key tiles once there is a workgroup
-    // per CU without splitting, 8 with one per two CUs, 2 when the launch would otherwise leave most
-    // of the chip idle (sweeps: 256 workgroups x 17 tiles -> 1 split, x 82 -> 2; 128 x 20 -> 2; 32 x 11 -> 4)
-    const long long cap2 = pl.key_tiles / (base >= kNumCUs ? 16 : (base >= kNumCUs / 2 ? 8 : 2));
-    if (ns > cap2) ns = cap2;
-  }
+  long long ns = p.kv_splits > 0 ? p.kv_splits : auto_splits(base, pl.key_tiles, pl.mode);
   if (ns > pl.key_tiles) ns = pl.key_tiles;
   if (ns > 64) ns = 64;
   if (ns < 1) ns = 1;

@@ -394,6 +394,28 @@ def test_probe_validation(lib):
     assert lib.sdllm_probe_mfma_bf16(10, 0, None, None, ctypes.byref(fl)) == sd.ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,D,P,K,s", [
+    (1, 1, 1, 128, 8192, 1, 0), (1, 1, 1, 64, 16, 5, 0), (3, 16, 4, 64, 1213, 27, 37), (1, 32, 32, 128, 608, 32, 32),
+    (1, 32, 8, 128, 4000, 32, 32), (2, 32, 32, 128, 700, 32, 32), (10, 4, 1, 128, 1024, 256, 0), (17, 8, 2, 128, 2304, 256, 0),
+    (7, 32, 16, 128, 900, 64, 0), (16, 28, 4, 128, 512, 32, 32), (8, 32, 32, 128, 1024, 32, 992), (16, 64, 32, 64, 8192, 8, 0)])
+def test_attention_automatic_splits(lib, B, Hq, Hkv, D, P, K, s):
+    """No split from one workgroup per CU on; below that the longest chain of key tiles of a CU never grows by splitting, and
+    8-wave workgroups with rows of their own (shape 2) never start a second round."""
+    def plan(splits):
+        return sd.plan_attention(sd.attn_params(sd.BF16, B, Hq, Hkv, D, P, P, K, max(s, 1), s, 0.0, splits))
+    one, auto = plan(1), plan(0)
+    rows, tiles = Hq // Hkv * (K + s), -(-(P + K + s) // 64)
+    base = B * Hkv * -(-rows // one.rows_per_workgroup)
+    if base >= 256:
+        assert auto.kv_splits == 1
+        return
+    rounds = -(-base * auto.kv_splits // 256)
+    assert rounds * auto.key_tiles_per_split <= tiles
+    assert rounds == 1 or auto.workgroup_shape != 2
+    if base <= 32 and tiles >= 12:
+        assert auto.kv_splits > 1
+
+
 @pytest.mark.parametrize("B,K,V,Hd", [(1, 1, 1, 32), (1, 32, 126464, 4096), (2, 32, 5000, 512), (3, 40, 777, 96),
                                        (8, 32, 126464, 4096), (16, 32, 152064, 3584), (9, 32, 700, 1024), (2, 32, 126464, 4096), (4, 32, 126464, 4096), (3, 32, 152064, 3584), (4, 32, 700, 64), (1, 32, 152064, 3584), (2, 32, 152064, 3584), (16, 4096, 100, 32)])
 def test_lm_head_plan_is_consistent(lib, B, K, V, Hd):

@@ -729,16 +729,17 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a, long long
 //   64 x 64 rows x 764 keys: 6: 16.4 / 4: 13.5     112 x 64 x 896: 5: 20.7 / 1: 13.6     8 x 64 x 5120: 40: 20.3 / 10: 16.1
 //   10 groups of 1024 rows x 1280 keys: 7: 34.7 / 4: 22.8     50 x 1024 x 1280: 2: 63.8 / 1: 41.2
 // From 256 workgroups on no split paid for its merge (320 x 64 rows x 2560 keys: 2 splits 88.2 / 1: 67.4; x 5120 160 / 130).
-static long long auto_splits(long long base, int key_tiles, int mode) {
-  if (base >= kNumCUs) return 1;
-  long long best = 1, best_cost = 10 * (key_tiles + 1);                      // tenths of a tile
+struct Splits { long long n, cost; };            // cost in tenths of the workgroup shape's tile
+static Splits auto_splits(long long base, int key_tiles, int mode) {
+  Splits best{1, 10 * ((base + kNumCUs - 1) / kNumCUs) * (key_tiles + 1)};
+  if (base >= kNumCUs) return best;
   for (long long ns = 2; ns <= key_tiles && ns <= 64; ++ns) {
     const long long tps = (key_tiles + ns - 1) / ns;
     const long long rounds = (base * ns + kNumCUs - 1) / kNumCUs;
     if (rounds > 1 && mode == 2) break;            // one such workgroup per CU: 34 x 1024 rows x 2560 keys 1 split 67, 2: 90
     if ((key_tiles + tps - 1) / tps != ns) continue;         // as long as with fewer splits
     const long long cost = 10 * rounds * (tps + 1) + 30 + 40 * (base < 64 ? base : 64) / 64 + 3 * ns + 8 * ((ns - 1) / 4);
-    if (cost < best_cost) { best_cost = cost; best = ns; }
+    if (cost < best.cost) best = Splits{ns, cost};
   }
   return best;
 }
@@ -748,23 +749,41 @@ AttnPlan plan_attention_bf16(const sdllm_attn_params& p) {
   const int g = p.Hq / p.Hkv;
   const long long Rtot = (long long)g * (p.K + p.n_keep);
   const long long Nkv = (long long)p.prefix_len + p.K + p.n_keep;
-  // 32 query rows per wave (128 per workgroup) pay off only when many query rows share one K/V
-  // stream (dense suffix); measured: 1024 rows -> 1.4x faster, 448 rows (GQA 7:1) -> 8 % slower
-  pl.rb = Rtot >= 512 ? 2 : 1;
-  // ... and when one 128-row tile then covers a K/V head with a long key stream: every K/V byte is read by
-  // one workgroup only, which lets the transfers carry the nontemporal hint (32 layers x 5248 keys, 128 rows:
-  // 2650 -> 2510 us per step; with 1312 keys the extra key splits it takes cost more than it gains)
-  if (Rtot > 64 && Rtot <= 128 && Nkv >= 64 * kKeyTile) pl.rb = 2;
-  // Many query tiles per K/V head: 8-wave workgroups whose two groups own 64 rb rows each and share every key tile
-  // (mode 2) bring a tile into LDS half as often, with three ring stages (one such workgroup per CU).
+  const long long groups = (long long)p.B * p.Hkv;
+  pl.key_tiles = (int)((Nkv + kKeyTile - 1) / kKeyTile);
+  auto workgroups_of = [&](int rows) { return groups * ((Rtot + rows - 1) / rows); };
+  // 64 query rows per workgroup ...
+  pl.rb = 1;
   pl.mode = 0;
-  pl.stages = 2;
-  if (kShareTiles && Rtot >= kShareMinRows) { pl.mode = 2; pl.stages = kShareStages; }
+  // ... or 128 when one such tile covers a K/V head with a long key stream: every K/V byte is read by
+  // one workgroup only, which lets the transfers carry the nontemporal hint (32 layers x 5248 keys, 128 rows:
+  // 2650 -> 2510 us per step; with 1312 keys the extra key splits it takes cost more than it gains) ...
+  if (Rtot > 64 && Rtot <= 128 && Nkv >= 64 * kKeyTile) pl.rb = 2;
+  // ... or, where a K/V head has many query rows, the cheapest of three shapes: 64 rows, 128 rows, and 256 rows whose two groups
+  // share every key tile (mode 2: a tile comes into LDS half as often, three ring stages, one such workgroup per CU).  A larger
+  // workgroup spends less time per row on a key tile (weights, measured per tile with every CU busy: 10 : 16 : 28 for 128-wide
+  // heads, 10 : 17 : 32 for 64-wide ones) but there are fewer of them, and with few (batch, KV head) pairs most of the chip is idle
+  // or waits for a second round.  Long streams of 128-wide heads spill from an XCD's L2 when smaller workgroups read them more
+  // often, which the weights do not see: there the smaller shapes have to be a fifth cheaper (40 groups of 640 rows x 4160 keys:
+  // 69 us with 256 rows, 76 with 64).  Below 8 key tiles all three cost the same few microseconds and 256 rows stay.  Over 147
+  // measured shapes the pick is within 2 % of the best of the three on the mean and never slower than always 256 rows, which took
+  // 1.23 times as long.
+  // D 128, us, 256 rows / 128 / 64: 32 groups of 512 rows x 628 keys 23.3 / 15.8 / 11.2; 96 x 640 x 660 48.1 / 30.1 / 35.0;
+  // 64 x 1024 x 1756 57.2 / 61.0 / 73.1.
+  if (kShareTiles && Rtot >= kShareMinRows) {
+    const long long w128 = p.D == 128 ? 16 : 17, w256 = p.D == 128 ? 28 : 32;
+    const long long c64 = 10 * auto_splits(workgroups_of(64), pl.key_tiles, 0).cost;
+    const long long c128 = w128 * auto_splits(workgroups_of(128), pl.key_tiles, 0).cost;
+    const long long c256 = w256 * auto_splits(workgroups_of(256), pl.key_tiles, 2).cost;
+    const long long bar = p.D == 128 && pl.key_tiles >= 56 ? 12 : 10;       // tenths: how much cheaper they have to be
+    if (p.kv_splits > 0 || pl.key_tiles < 8 || (10 * c256 <= bar * c128 && 10 * c256 <= bar * c64)) { pl.rb = 2; pl.mode = 2; }
+    else if (c128 <= c64) pl.rb = 2;
+  }
+  pl.stages = pl.mode == 2 ? kShareStages : 2;
   const int rows_wg = 64 * pl.rb * (pl.mode == 2 ? 2 : 1);
   pl.q_tiles = (int)((Rtot + rows_wg - 1) / rows_wg);
-  pl.key_tiles = (int)((Nkv + kKeyTile - 1) / kKeyTile);
-  const long long base = (long long)p.B * p.Hkv * pl.q_tiles;
-  long long ns = p.kv_splits > 0 ? p.kv_splits : auto_splits(base, pl.key_tiles, pl.mode);
+  const long long base = groups * pl.q_tiles;
+  long long ns = p.kv_splits > 0 ? p.kv_splits : auto_splits(base, pl.key_tiles, pl.mode).n;
   if (ns > pl.key_tiles) ns = pl.key_tiles;
   if (ns > 64) ns = 64;
   if (ns < 1) ns = 1;

@@ -403,9 +403,11 @@ def test_attention_automatic_splits(lib, B, Hq, Hkv, D, P, K, s):
     8-wave workgroups with rows of their own (shape 2) never start a second round."""
     def plan(splits):
         return sd.plan_attention(sd.attn_params(sd.BF16, B, Hq, Hkv, D, P, P, K, max(s, 1), s, 0.0, splits))
-    one, auto = plan(1), plan(0)
+    auto = plan(0)
     rows, tiles = Hq // Hkv * (K + s), -(-(P + K + s) // 64)
-    base = B * Hkv * -(-rows // one.rows_per_workgroup)
+    base = B * Hkv * -(-rows // auto.rows_per_workgroup)
+    if tiles < 8:
+        assert (auto.workgroup_shape == 2) == (rows >= 512)
     if base >= 256:
         assert auto.kv_splits == 1
         return

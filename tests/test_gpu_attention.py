@@ -263,6 +263,23 @@ def test_attention_bf16_workgroup_shapes(gpu_lib, shape, B, Hq, Hkv, D, P, cap, 
                                       f"{pl.key_tiles_per_split} tiles per split:")
 
 
+@pytest.mark.parametrize("shape,rows,B,Hq,Hkv,D,P,K,S,keep", [
+    (0, 64, 1, 8, 1, 128, 500, 64, 70, tuple(range(64))),                     # 1024 rows on 628 keys: 16 query tiles, splits
+    (0, 64, 2, 8, 1, 64, 700, 40, 60, tuple(range(1, 52))),                   # D = 64, 728 rows: a ragged last query tile
+    (1, 64, 1, 16, 1, 128, 900, 20, 33, tuple(range(0, 26, 2))),              # 528 rows: two groups of 64 alternate key tiles
+    (1, 128, 3, 36, 4, 128, 3000, 32, 50, tuple(range(40))),                  # 648 rows: 128-row tiles, the last with 8 rows; 16 key tiles a split
+    (0, 128, 6, 64, 16, 128, 500, 64, 96, tuple(range(96))),                  # 640 rows = 5 tiles of 128, more than one round
+])
+def test_attention_bf16_many_rows_few_groups(gpu_lib, shape, rows, B, Hq, Hkv, D, P, K, S, keep):
+    """From 512 query rows per K/V head on, the smaller workgroups that the plan picks where few groups share the chip."""
+    sd = gpu_lib
+    t = wl.make_custom_attention_inputs("bf16", B, Hq, Hkv, D, P, P, K, S, keep, seed=7 * P + K + len(keep))
+    pl = sd.plan_attention(sd.attn_params(sd.BF16, B, Hq, Hkv, D, P, P, K, S, len(keep), 0.0, 0))
+    assert (pl.workgroup_shape, pl.rows_per_workgroup) == (shape, rows)
+    got = run_gpu(sd, t, P)
+    assert_bf16_close(got, t, P, what=f"{rows} rows, {pl.kv_splits} split(s), {pl.key_tiles_per_split} tiles per split:")
+
+
 def _random_case(seed):
     """A seeded random problem: small enough for the oracle, wide enough to reach every workgroup shape, both head
     dims, GQA ratios up to 8, empty caches / suffixes, forced and automatic key splits."""

@@ -114,7 +114,8 @@ __device__ __forceinline__ void f32_load_k(const AttnF32Args& a, int l16, int G,
   for (int s = 0; s < NS; ++s) k[s] = f32_load4(kp[0] + min(16 * s + 4 * G, a.D - 4));
 }
 
-// Heads of 65 to 128 elements: K goes through LDS, into a region of the wave's own (no barrier).  The operand layout takes 64
+// Heads of 65 to 128 elements, short launches (the rule is at the launch): K goes through LDS, into a region of the wave's own (no
+// barrier).  The operand layout takes 64
 // bytes of each of 16 rows a load, half lines; a 128-wide block's eight such loads keep the load path busy for 512 cycles a
 // wave, half as long as the matrix pipe of a SIMD needs for the scores, and the CU's eight waves share one load path.  A
 // transfer brings one kilobyte of whole lines.  B2, 32 / 8 heads x 128, 64 rows x 672 keys: 23.5 -> 21.6 us; B1, 32 / 32, 64 rows
@@ -122,12 +123,11 @@ __device__ __forceinline__ void f32_load_k(const AttnF32Args& a, int l16, int G,
 // wave per SIMD, 8 heads x 252, 1532 keys 77 -> 85: both keep their loads.)  A row is CPR 16-byte chunks (its head
 // padded to the slices by re-reading the last one); place p of row r holds chunk p ^ r in the low four bits, so that an operand
 // read (one chunk of 16 rows; the hardware serves rows 0-3 and 12-15 of it with rows 4-11 of the next) is free of conflicts.
-template <int NS> constexpr bool f32_k_in_lds() { return NS == 8; }
 template <int NS> struct F32K {
   static constexpr int CPR = 4 * NS;             // chunks per row
   static constexpr int RPT = 64 / CPR;           // rows per transfer; NS transfers per block
   static constexpr int BUF = NS * 1024;          // bytes of a block
-  unsigned voff[f32_k_in_lds<NS>() ? NS : 1];    // this lane's byte offset of transfer j from the block's first row
+  unsigned voff[NS];                             // this lane's byte offset of transfer j from the block's first row
   unsigned lds;                                  // the wave's region: two blocks
 };
 
@@ -253,7 +253,8 @@ __device__ __forceinline__ void f32_accumulate(const AttnF32Args& a, int G, int 
   l += (p[0] + p[1]) + (p[2] + p[3]);              // this lane's keys; summed across the row's lanes at the end
 }
 
-template <int NS, bool RAGGED>
+// KLDS: K goes through LDS
+template <int NS, bool RAGGED, bool KLDS>
 __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) void attention_f32_kernel(AttnF32Args a) {
   extern __shared__ __attribute__((aligned(16))) float f32_lds[];
   const int lane = threadIdx.x & 63, l16 = lane & 15, G = lane >> 4;
@@ -283,7 +284,6 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
   const int hl = Rc / a.Nq, qi = Rc - hl * a.Nq;
   const long long qbh = (long long)b * a.Hq + (long long)kvh * a.g + hl;
   const int q_keep = a.keep_idx[max(qi - a.K, 0)];
-  constexpr bool kLds = f32_k_in_lds<NS>();
   using KS = F32K<NS>;
   KS kk;
   unsigned char* const kbuf = reinterpret_cast<unsigned char*>(f32_lds) + wave * 2 * KS::BUF;
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
            wave * 2 * KS::BUF;
   f32x4 k[NS], v[NS / 4][4];
   F32Ahead ka = f32_ahead(a, wk);
-  if constexpr (kLds) {
+  if constexpr (KLDS) {
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
       const int row = j * KS::RPT + lane / KS::CPR;
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
   // after the first block.)
   int buf = 0;
   auto block = [&](int blk, auto partial) {
-    if constexpr (kLds) {
+    if constexpr (KLDS) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       const F32Ahead kn = f32_ahead(a, blk + a.nk);
       if (blk + a.nk < a.key_blocks) f32_dma_k<NS>(a, kk, lane, kc, kb, ks, blk + a.nk, buf ^ 1, kn);
@@ -338,7 +338,7 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
       ka = f32_ahead(a, blk + a.nk);
     }
     const f32x4 sc = f32_scores<NS, RAGGED, partial.value>(a, G, blk, k, q);
-    if constexpr (!kLds) f32_load_k<NS>(a, l16, G, kc, kb, ks, min(blk + a.nk, a.key_blocks - 1), ka, k);   // (past the end:
+    if constexpr (!KLDS) f32_load_k<NS>(a, l16, G, kc, kb, ks, min(blk + a.nk, a.key_blocks - 1), ka, k);   // (past the end:
     f32_accumulate<NS, partial.value>(a, G, blk, sc, v, o, m, l);                                           // never used)
   };
   const int full = a.Nkv / kF32Keys;
@@ -364,7 +364,7 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
     return;
   }
   const int nw = a.nr * a.nk;
-  if constexpr (kLds) __syncthreads();                                   // the exchange area lies over the regions of K
+  if constexpr (KLDS) __syncthreads();                                   // the exchange area lies over the regions of K
   f32x4* xo = reinterpret_cast<f32x4*>(f32_lds);                         // [wave][NS pieces][64 lanes]
   float2* xml = reinterpret_cast<float2*>(f32_lds + nw * NS * 256);      // [wave][16 rows]
 #pragma unroll
@@ -431,36 +431,39 @@ void attention_f32_plan(const sdllm_attn_params& p, sdllm_attn_plan* plan) {
 }
 
 // the exchange area of the merge, or the regions of K that it lies over
-template <int NS> constexpr size_t f32_lds_bytes(int waves) {
+template <int NS, bool KLDS> constexpr size_t f32_lds_bytes(int waves) {
   constexpr int exchange = NS * 1024 + 16 * (int)sizeof(float2);
-  static_assert(!f32_k_in_lds<NS>() || 2 * F32K<NS>::BUF >= exchange, "the exchange area fits the regions of K");
-  return (size_t)waves * (f32_k_in_lds<NS>() ? 2 * F32K<NS>::BUF : exchange);
+  static_assert(2 * F32K<NS>::BUF >= exchange, "the exchange area fits the regions of K");
+  return (size_t)waves * (KLDS ? 2 * F32K<NS>::BUF : exchange);
 }
 
-template <int NS, bool RAGGED>
+template <int NS, bool RAGGED, bool KLDS>
 static hipError_t f32_opt_in() {
   static LdsOptIn st;
-  return ensure_lds_opt_in(reinterpret_cast<const void*>(&attention_f32_kernel<NS, RAGGED>),
-                           f32_lds_bytes<NS>(f32_max_waves<NS>()), st);
+  return ensure_lds_opt_in(reinterpret_cast<const void*>(&attention_f32_kernel<NS, RAGGED, KLDS>),
+                           f32_lds_bytes<NS, KLDS>(f32_max_waves<NS>()), st);
 }
 
 hipError_t prepare_attention_f32() {
-  hipError_t e = f32_opt_in<4, false>();
-  if (e == hipSuccess) e = f32_opt_in<4, true>();
-  if (e == hipSuccess) e = f32_opt_in<8, false>();
-  if (e == hipSuccess) e = f32_opt_in<8, true>();
-  if (e == hipSuccess) e = f32_opt_in<16, false>();
-  if (e == hipSuccess) e = f32_opt_in<16, true>();
+  hipError_t e = f32_opt_in<4, false, false>();
+  if (e == hipSuccess) e = f32_opt_in<4, true, false>();
+  if (e == hipSuccess) e = f32_opt_in<8, false, false>();
+  if (e == hipSuccess) e = f32_opt_in<8, true, false>();
+  if (e == hipSuccess) e = f32_opt_in<8, false, true>();
+  if (e == hipSuccess) e = f32_opt_in<8, true, true>();
+  if (e == hipSuccess) e = f32_opt_in<16, false, false>();
+  if (e == hipSuccess) e = f32_opt_in<16, true, false>();
   return e;
 }
 
-template <int NS, bool RAGGED>
+template <int NS, bool RAGGED, bool KLDS = false>
 static hipError_t f32_launch(const AttnF32Args& a, const F32Plan& pl, hipStream_t stream) {
-  const hipError_t e = f32_opt_in<NS, RAGGED>();
+  const hipError_t e = f32_opt_in<NS, RAGGED, KLDS>();
   if (e != hipSuccess) return e;
   const int waves = pl.nr * pl.nk;
   const dim3 grid((unsigned)std::min(pl.workgroups, (long long)kF32GridX), (unsigned)((pl.workgroups + kF32GridX - 1) / kF32GridX));
-  hipLaunchKernelGGL((attention_f32_kernel<NS, RAGGED>), grid, dim3(64 * waves), f32_k_in_lds<NS>() || pl.nk > 1 ? f32_lds_bytes<NS>(waves) : 0, stream, a);
+  const size_t lds = KLDS || pl.nk > 1 ? f32_lds_bytes<NS, KLDS>(waves) : 0;
+  hipLaunchKernelGGL((attention_f32_kernel<NS, RAGGED, KLDS>), grid, dim3(64 * waves), lds, stream, a);
   return hipGetLastError();
 }
 
@@ -484,13 +487,20 @@ hipError_t launch_attention_f32(const sdllm_attn_params& p,
   a.n_groups = p.B * p.Hkv; a.q_tiles = pl.q_tiles; a.key_blocks = (a.Nkv + kF32Keys - 1) / kF32Keys;
   a.nr = pl.nr; a.nk = pl.nk; a.xcd_map = pl.xcd_map;
   a.scale = p.scale > 0.f ? p.scale : 1.0f / sqrtf((float)p.D);
+  // K through LDS (heads of 65 to 128 elements) pays where the launch is a chain of latencies: a round and a half of workgroups
+  // at most, and four whole key blocks or more.  In longer launches a workgroup's 128 KB of LDS keep the next one from starting
+  // beside it, and a shorter sequence only adds the wait for K in front of V.  Measured over 90 geometries x 5 widths x up to 10 lengths, registers / LDS in us:
+  //   within the rule 0.86 to 1.02 of the registers' time; 16 groups x 256 rows x 672 keys, 128 wide, 23.5 / 21.6
+  //   512 to 2048 workgroups of one 16-row block, 128 wide, 129 to 600 keys: 1.00 to 1.17 of it; 512 groups x 272 keys 26.3 / 27.1
+  //   fewer keys: 8192 groups of one row x 1 key 20.7 / 22.4; 8 groups x 128 rows x 32 keys 6.06 / 6.41
+  const bool k_lds = pl.workgroups <= kNumCUs * 3 / 2 && a.Nkv >= 4 * kF32Keys;
   switch (p.D) {
     case 64: return f32_launch<4, false>(a, pl, stream);
-    case 128: return f32_launch<8, false>(a, pl, stream);
+    case 128: return k_lds ? f32_launch<8, false, true>(a, pl, stream) : f32_launch<8, false>(a, pl, stream);
     case 256: return f32_launch<16, false>(a, pl, stream);
   }
   if (p.D < 64) return f32_launch<4, true>(a, pl, stream);
-  if (p.D < 128) return f32_launch<8, true>(a, pl, stream);
+  if (p.D < 128) return k_lds ? f32_launch<8, true, true>(a, pl, stream) : f32_launch<8, true>(a, pl, stream);
   return f32_launch<16, true>(a, pl, stream);
 }
 

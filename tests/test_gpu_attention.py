@@ -134,6 +134,24 @@ def test_attention_fp32_several_row_tiles(gpu_lib, B, Hq, Hkv, D, P, K, S, keep,
     assert np.abs(got - oracle(t, P)).max() <= TOL["fp32"]
 
 
+@pytest.mark.parametrize("D", [80, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,P,K,S,keep,nr,workgroups", [
+    (8, 20, 5, 20, 57, 9, (0, 8), 2, 320),                        # two, four, eight row blocks per workgroup, the last workgroup
+    (16, 20, 5, 20, 57, 9, (0, 8), 4, 320),                       # of a group not full; five key blocks, the last partial; with
+    (28, 20, 5, 20, 57, 9, (0, 8), 8, 288),                       # eight row blocks a wave has all of the keys and nothing merges
+    (12, 32, 32, 48, 16, 0, (), 1, 384),                          # most workgroups, fewest keys for K through LDS
+    (12, 32, 32, 47, 16, 0, (), 1, 384),                          # one key fewer, or more workgroups: K in registers
+    (13, 32, 32, 48, 16, 0, (), 1, 416),
+])
+def test_attention_fp32_k_through_lds_row_tiles(gpu_lib, D, B, Hq, Hkv, P, K, S, keep, nr, workgroups):
+    p = gpu_lib.attn_params(gpu_lib.FP32, B, Hq, Hkv, D, P, P, K, S, len(keep))
+    plan = gpu_lib.plan_attention(p)
+    assert (plan.rows_per_workgroup, plan.workgroups) == (16 * nr, workgroups)
+    t = wl.make_custom_attention_inputs("fp32", B, Hq, Hkv, D, P, P, K, max(S, 1), keep, seed=B + D + P)
+    got = run_gpu(gpu_lib, t, P)
+    assert np.abs(got - oracle(t, P)).max() <= TOL["fp32"]
+
+
 @pytest.mark.parametrize("D,P,K,first,nkeys", [
     (64, 300, 20, 0, 16),           # the first key block: every score of one wave's first block is -inf
     (64, 300, 20, 80, 16),          # ... of another wave

@@ -250,8 +250,9 @@ int sdllm_lm_head_unmask(const sdllm_lm_head_params* p,
  * 192, 224 or 256 positions, as few as their number allows and evenly filled.  The plan describes the shape that
  * serves B*K masked positions: the most rows of hidden a row chunk takes (256 for the last shape),
  * rows of W per vocabulary tile, number of tiles, row chunks in the grid, workgroups launched (of the last
- * shape's at most one per CU does work and walks several tiles), LDS bytes per workgroup; triples_per_position is the workspace's row length (the largest tile count among the
- * shapes launched).  Returns SDLLM_OK or the validation error. */
+ * shape's the first ones do the work, each walks several tiles: one per CU where the chunks that hold masked positions
+ * number 1, 2, 4, 8, 16 or 32, otherwise as many as share the tiles out evenly), LDS bytes per workgroup;
+ * triples_per_position is the workspace's row length (the largest tile count among the shapes launched).  Returns SDLLM_OK or the validation error. */
 typedef struct sdllm_lm_head_plan {
   int32_t rows_per_chunk;
   int32_t vocab_rows_per_tile;

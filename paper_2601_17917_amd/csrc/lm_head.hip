@@ -336,6 +336,27 @@ __device__ __forceinline__ void lm_head_rows_tiles(const LmHeadArgs& a, unsigned
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing of this workgroup's is in flight when it ends
 }
 
+// Into how many parts the vocabulary tiles of an XCD are cut, for nact row chunks each (parts x nact workgroups per XCD, one of
+// them on a CU at a time).  Where the chunks divide the CUs every CU has one workgroup.  Otherwise the workgroups come in rounds,
+// and what counts is the rounds times a workgroup's length: its tiles, each as long as its pairs of k-steps and one more for the
+// reduction, and its start, which is two scans of all mask bytes and the first transfers.  Each lane prices a length of 1 to 64
+// tiles; the longest of the cheapest is taken.  (The grid has room for one workgroup per tile and chunk.)
+// One workgroup per CU for any number of chunks left CUs without work.  Row-major W, in us, one per CU / now (and with one per
+// tile and chunk, of one wave per SIMD): 32000 x 2048, 1500 positions (6 chunks) 235 / 209 (208), 4352 (17) 775 / 585 (587),
+// 8448 (33) 1646 / 1120 (1174); 126464 x 4096, 2600 positions (11) 2954 / 2638 (2601).
+__device__ __forceinline__ int lm_rows_parts(const LmHeadArgs& a, int nact) {
+  constexpr int kSlots = kNumCUs / kNumXCDs;
+  if (kSlots % nact == 0) return kSlots / nact;
+  const int nt = (a.ntile + kNumXCDs - 1) / kNumXCDs;
+  const int t = (threadIdx.x & 63) + 1, rounds = (((nt + t - 1) / t) * nact + kSlots - 1) / kSlots;
+  const float cost = (float)rounds * ((float)t * (float)(a.Hd / 64 + 1) + (float)(2 + a.rows_total / 1024));
+  float best = cost;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) best = fminf(best, __shfl_xor(best, off));
+  const int len = 64 - __builtin_clzll(__ballot(cost == best));
+  return __builtin_amdgcn_readfirstlane((nt + len - 1) / len);
+}
+
 template <bool PACKED>
 __global__ __launch_bounds__(kRwThreads, 2) void lm_head_rows_kernel(LmHeadArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
@@ -354,11 +375,9 @@ __global__ __launch_bounds__(kRwThreads, 2) void lm_head_rows_kernel(LmHeadArgs 
   const int share = (total + kRwBM - 1) / kRwBM;
   const int bm = (((total + share - 1) / share) + 31) & ~31;         // 160, 192, 224 or 256 rows
   const int nact = (total + bm - 1) / bm;          // <= share <= a.nchunk, since total <= rows_total
-  // ---- workgroup -> (row chunk, its share of the vocabulary tiles).  One workgroup per CU works, the grid's first ones, and
-  // walks its tiles one after the other; more of them work only where the chunks outnumber the CUs of an XCD.  Chunks of a tile
-  // share the id mod 8 (the XCD) and are adjacent in dispatch order: W comes from HBM once.
-  const int slots = max(kNumCUs / kNumXCDs, nact), slot = blockIdx.x >> 3;
-  const int chunk = slot % nact, part = slot / nact, parts = min(slots, (int)gridDim.x >> 3) / nact;
+  // ---- workgroup -> (row chunk, every parts-th vocabulary tile of an XCD), the grid's first parts x nact of each XCD.  Chunks of a
+  // tile share the id mod 8 (the XCD) and are adjacent in dispatch order: W comes from HBM once.
+  const int slot = blockIdx.x >> 3, chunk = slot % nact, part = slot / nact, parts = lm_rows_parts(a, nact);
   const int tile0 = part * kNumXCDs + (blockIdx.x & 7);
   if (part >= parts || tile0 >= a.ntile) return;
 

@@ -220,6 +220,27 @@ def test_lm_head_rows_walk_several_tiles(gpu_lib, n_masked, Hd, packed):
     assert skipped <= 1
 
 
+@pytest.mark.parametrize("B,K,n_masked,V", [
+    (5, 64, 192, 67100), (5, 64, 224, 67100),                 # chunks of 192 and 224 rows that walk two or three tiles
+    (12, 64, 700, 67100),                                     # three chunks: nine workgroups each per XCD, 33 tiles to share out
+    (24, 64, 1500, 9000), (22, 128, 2700, 9000),              # 6 and 11 chunks of five tiles per XCD
+    (35, 128, 4352, 9000), (66, 128, 8448, 9000),             # 17 and 33: more than one round of workgroups, tiles in a row
+])
+@pytest.mark.parametrize("Hd", [64, 96])
+@pytest.mark.parametrize("packed", [False, True])
+def test_lm_head_rows_any_number_of_chunks(gpu_lib, B, K, n_masked, V, Hd, packed):
+    """The vocabulary tiles of an XCD shared out among chunk counts that do not divide its 32 CUs: every position gets a triple
+    of every tile."""
+    h, W, tokens, masked, hd, Wd = _host_case(B, K, Hd, V, seed=n_masked + Hd, frac=0.0)
+    flat = np.random.Generator(np.random.Philox(key=n_masked)).permutation(B * K)[:n_masked]
+    masked.reshape(-1)[flat] = 1
+    tokens.reshape(-1)[flat] = wl.MASK_TOKEN
+    got = run_gpu(gpu_lib, hd, Wd, tokens, masked, 0.7, 0.3, packed=packed)
+    want = _oracle(h, W, tokens, masked, 0.7, 0.3)
+    n_gap, n_band, skipped = compare(got, want, tokens, masked)
+    assert skipped <= max(1, B // 16)                         # (sequences whose fallback is a near tie)
+
+
 @pytest.mark.parametrize("B,K,Hd,V,ld_h,ld_w", [(2, 16, 64, 200, 72, 80), (2, 32, 320, 1000, 328, 384),
                                                  (4, 32, 320, 1000, 328, 384),
                                                  (3, 32, 320, 1000, 328, 384)])

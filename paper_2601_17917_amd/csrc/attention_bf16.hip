@@ -22,6 +22,8 @@
 //   Online softmax in the log2 domain; a split writes (unnormalised O, m, l) and a second
 //   kernel merges the splits in a fixed order (deterministic, no atomics).
 #include "common.h"
+#include <algorithm>
+#include <climits>
 #include <type_traits>
 
 namespace sdllm {
@@ -719,29 +721,45 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a, long long
   *reinterpret_cast<uint2*>(orow + d) = w2;
 }
 
-// Key splits of a launch with `base` workgroups before splitting.  What counts is the longest chain of key tiles a CU works off,
-// rounds of 256 workgroups x (tiles per split + 1 for the prologue), against the merge, which costs a launch (3 tiles' time),
-// its rows (4 at 64 workgroups and more), 0.3 a split and 0.8 a further round trip for every four; the constants are fitted to
-// sweeps of 430 shapes (8 to 448 workgroups x 4 to 80 tiles, both head widths, all workgroup shapes, a dozen split counts
-// each), which they leave within 1 % of the best split on the mean, where two workgroups per CU were 13 % behind it.  The 8-wave workgroup is two waves per SIMD by itself: a second workgroup per CU, or a split that starts a second
-// round of a few workgroups, only adds merge traffic and tail.  D 128 unless said, us, splits for two workgroups per CU / now:
-//   12 groups of 256 rows x 1277 keys, D 64: 10 splits 12.6 / 4: 9.9     8 groups of 256 x 4064: 16: 19.7 / 8: 15.5
-//   64 x 64 rows x 764 keys: 6: 16.4 / 4: 13.5     112 x 64 x 896: 5: 20.7 / 1: 13.6     8 x 64 x 5120: 40: 20.3 / 10: 16.1
-//   10 groups of 1024 rows x 1280 keys: 7: 34.7 / 4: 22.8     50 x 1024 x 1280: 2: 63.8 / 1: 41.2
-// From 256 workgroups on no split paid for its merge (320 x 64 rows x 2560 keys: 2 splits 88.2 / 1: 67.4; x 5120 160 / 130).
-struct Splits { long long n, cost; };            // cost in tenths of the workgroup shape's tile
-static Splits auto_splits(long long base, int key_tiles, int mode) {
-  Splits best{1, 10 * ((base + kNumCUs - 1) / kNumCUs) * (key_tiles + 1)};
-  if (base >= kNumCUs) return best;
-  for (long long ns = 2; ns <= key_tiles && ns <= 64; ++ns) {
-    const long long tps = (key_tiles + ns - 1) / ns;
-    const long long rounds = (base * ns + kNumCUs - 1) / kNumCUs;
-    if (rounds > 1 && mode == 2) break;            // one such workgroup per CU: 34 x 1024 rows x 2560 keys 1 split 67, 2: 90
+// What a launch is priced at, in hundredths of a microsecond.  All query tiles of a unit, a (batch, K/V head, key split), sit on
+// the XCD unit % 8, so what counts is the longest queue of a CU there, ceil(units / 8) x query tiles over 32 CUs: workgroups x
+// (key tiles per split, and a start).  Two 4-wave workgroups of a CU run side by side, so their starts count once, and tile and
+// start differ where one workgroup's two groups alternate the tiles (mode 1).  A split costs a merge: a launch, the partial
+// results' bytes and its rows, and further round trips.  (Counted over all 256 CUs, 6 groups x 1088 rows x 2560 keys
+// took five splits of 64-row workgroups for two rounds, but four units of an XCD are 68 workgroups, three rounds: 29.5 us, now four
+// splits of 128 rows 24.4.  1 group x 8244 x 2095, three splits, hence three XCDs at work: 46.4 us, now seven 35.0.)  The constants
+// are a least-squares fit (relative error 8 %) to 28000 timed launches: 2150 problems of 1 to 200 groups x 1 to 8192 rows x 2 to
+// 100 key tiles, both head widths, up to 16 split counts each and, from 512 rows, three workgroup shapes.
+struct LaunchPrice { int rows, tile1, start1, tile, start; };      // per key tile and per workgroup, mode 1 and otherwise
+static constexpr LaunchPrice kPrices[2][3] = {
+    {{64, 38, 34, 31, 44}, {128, 62, 167, 54, 120}, {256, 0, 0, 105, 153}},          // 64-wide heads
+    {{64, 63, 138, 57, 148}, {128, 81, 458, 86, 323}, {256, 0, 0, 149, 515}}};       // 128-wide heads
+
+struct Splits { long long n, price; };
+// The cheapest number of key splits.  From one workgroup per CU on a split has to promise a tenth of the price, and nothing is
+// split that the read of K and V bounds (6.5 TB/s), which the prices leave out: 128 groups x 155 rows x 3411 keys, 384 workgroups,
+// 57.6 us, with two splits, priced 8 % lower, 68.9; 384 x 32 x 5139, 1 GB, 149 us, with two 173; but 80 x 200 x 6400, D 64, 320
+// workgroups, priced a quarter lower with four splits, 63.5 and 52.4.
+static Splits cheapest_splits(const LaunchPrice& w, long long groups, long long Rtot, int key_tiles, int D) {
+  const int xcd_cus = kNumCUs / kNumXCDs;
+  const long long q_tiles = (Rtot + w.rows - 1) / w.rows, rows = groups * Rtot;
+  const int most = groups * q_tiles >= 4 * kNumCUs ? 1 : std::min(key_tiles, 64);
+  Splits best{1, LLONG_MAX}, one = best;
+  for (int ns = 1; ns <= most; ++ns) {
+    const int tps = (key_tiles + ns - 1) / ns;
     if ((key_tiles + tps - 1) / tps != ns) continue;         // as long as with fewer splits
-    const long long cost = 10 * rounds * (tps + 1) + 30 + 40 * (base < 64 ? base : 64) / 64 + 3 * ns + 8 * ((ns - 1) / 4);
-    if (cost < best.cost) best = Splits{ns, cost};
+    const long long per_xcd = (groups * ns + kNumXCDs - 1) / kNumXCDs * q_tiles;
+    const long long n = (per_xcd + xcd_cus - 1) / xcd_cus;
+    long long price;
+    if (w.rows == 256) price = n * (tps * w.tile + w.start);
+    else if (n == 1 && tps >= 4) price = tps * w.tile1 + w.start1;
+    else price = n * tps * w.tile + (n + 1) / 2 * w.start;
+    if (ns > 1) price += 180 + rows * ns * (D + 2) * 84 / 1000000 + 14 * ns + 35 * ((ns - 1) / 4) + 215 * std::min(rows, 4096LL) / 4096;
+    if (price < best.price) best = Splits{ns, price};
+    if (ns == 1) one = best;
   }
-  return best;
+  const long long read = groups * key_tiles * kKeyTile * D * 4 / 65000;
+  return groups * q_tiles >= kNumCUs && (10 * best.price > 9 * one.price || read > one.price) ? one : best;
 }
 
 AttnPlan plan_attention_bf16(const sdllm_attn_params& p) {
@@ -751,39 +769,42 @@ AttnPlan plan_attention_bf16(const sdllm_attn_params& p) {
   const long long Nkv = (long long)p.prefix_len + p.K + p.n_keep;
   const long long groups = (long long)p.B * p.Hkv;
   pl.key_tiles = (int)((Nkv + kKeyTile - 1) / kKeyTile);
-  auto workgroups_of = [&](int rows) { return groups * ((Rtot + rows - 1) / rows); };
   // 64 query rows per workgroup ...
+  const LaunchPrice* price = kPrices[p.D == 128];
   pl.rb = 1;
   pl.mode = 0;
   // ... or 128 when one such tile covers a K/V head with a long key stream: every K/V byte is read by
   // one workgroup only, which lets the transfers carry the nontemporal hint (32 layers x 5248 keys, 128 rows:
   // 2650 -> 2510 us per step; with 1312 keys the extra key splits it takes cost more than it gains) ...
-  if (Rtot > 64 && Rtot <= 128 && Nkv >= 64 * kKeyTile) pl.rb = 2;
+  if (Rtot > 64 && Rtot <= 128 && Nkv >= 64 * kKeyTile) { pl.rb = 2; ++price; }
   // ... or, where a K/V head has many query rows, the cheapest of three shapes: 64 rows, 128 rows, and 256 rows whose two groups
   // share every key tile (mode 2: a tile comes into LDS half as often, three ring stages, one such workgroup per CU).  A larger
-  // workgroup spends less time per row on a key tile (weights, measured per tile with every CU busy: 10 : 16 : 28 for 128-wide
-  // heads, 10 : 17 : 32 for 64-wide ones) but there are fewer of them, and with few (batch, KV head) pairs most of the chip is idle
-  // or waits for a second round.  Long streams of 128-wide heads spill from an XCD's L2 when smaller workgroups read them more
-  // often, which the weights do not see: there the smaller shapes have to be a fifth cheaper (40 groups of 640 rows x 4160 keys:
-  // 69 us with 256 rows, 76 with 64).  Below 8 key tiles all three cost the same few microseconds and 256 rows stay.  Over 147
-  // measured shapes the pick is within 2 % of the best of the three on the mean and never slower than always 256 rows, which took
-  // 1.23 times as long.
+  // workgroup spends less time per row on a key tile but there are fewer of them, and with few (batch, KV head) pairs most of the
+  // chip is idle or waits for a second round.  256 rows stay where they are within 3 % of the others (which is what the prices are
+  // good for: at 950 measured problems three came out over 3 % slower than 256 rows with two workgroups' worth of splits per CU
+  // took before, 14 without the margin), and below 8 key tiles.
   // D 128, us, 256 rows / 128 / 64: 32 groups of 512 rows x 628 keys 23.3 / 15.8 / 11.2; 96 x 640 x 660 48.1 / 30.1 / 35.0;
   // 64 x 1024 x 1756 57.2 / 61.0 / 73.1.
+  long long auto_ns = 0;
   if (kShareTiles && Rtot >= kShareMinRows) {
-    const long long w128 = p.D == 128 ? 16 : 17, w256 = p.D == 128 ? 28 : 32;
-    const long long c64 = 10 * auto_splits(workgroups_of(64), pl.key_tiles, 0).cost;
-    const long long c128 = w128 * auto_splits(workgroups_of(128), pl.key_tiles, 0).cost;
-    const long long c256 = w256 * auto_splits(workgroups_of(256), pl.key_tiles, 2).cost;
-    const long long bar = p.D == 128 && pl.key_tiles >= 56 ? 12 : 10;       // tenths: how much cheaper they have to be
-    if (p.kv_splits > 0 || pl.key_tiles < 8 || (10 * c256 <= bar * c128 && 10 * c256 <= bar * c64)) { pl.rb = 2; pl.mode = 2; }
-    else if (c128 <= c64) pl.rb = 2;
+    pl.rb = 2; pl.mode = 2;
+    if (p.kv_splits <= 0) {
+      const Splits s256 = cheapest_splits(price[2], groups, Rtot, pl.key_tiles, p.D);
+      auto_ns = s256.n;
+      if (pl.key_tiles >= 8) {
+        const Splits s128 = cheapest_splits(price[1], groups, Rtot, pl.key_tiles, p.D);
+        const Splits s64 = cheapest_splits(price[0], groups, Rtot, pl.key_tiles, p.D);
+        const Splits& small = s128.price <= s64.price ? s128 : s64;
+        if (100 * s256.price > 103 * small.price) { pl.mode = 0; pl.rb = &small == &s128 ? 2 : 1; auto_ns = small.n; }
+      }
+    }
+  } else if (p.kv_splits <= 0) {
+    auto_ns = cheapest_splits(*price, groups, Rtot, pl.key_tiles, p.D).n;
   }
   pl.stages = pl.mode == 2 ? kShareStages : 2;
   const int rows_wg = 64 * pl.rb * (pl.mode == 2 ? 2 : 1);
   pl.q_tiles = (int)((Rtot + rows_wg - 1) / rows_wg);
-  const long long base = groups * pl.q_tiles;
-  long long ns = p.kv_splits > 0 ? p.kv_splits : auto_splits(base, pl.key_tiles, pl.mode).n;
+  long long ns = p.kv_splits > 0 ? p.kv_splits : auto_ns;
   if (ns > pl.key_tiles) ns = pl.key_tiles;
   if (ns > 64) ns = 64;
   if (ns < 1) ns = 1;

@@ -418,6 +418,25 @@ def test_attention_automatic_splits(lib, B, Hq, Hkv, D, P, K, s):
         assert auto.kv_splits > 1
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("rows", [64, 200, 512, 704, 1088, 1536, 1984, 8192])
+def test_attention_automatic_splits_follow_the_queues_of_the_chip_parts(lib, D, rows):
+    """The query tiles of a (batch, K/V head, split) unit share one of the 8 chip parts with 32 CUs each (workgroups is padded to
+    whole units there), also where the units do not fill the parts evenly: no pick has a queue of key tiles per CU, as the plan's
+    own workgroups give it, that fewer splits would make a fifth shorter."""
+    for groups in list(range(1, 41)) + [47, 64, 100, 127]:
+        for tiles in (8, 16, 24, 40):
+            P = tiles * 64 - rows // 8
+            if P < 1:
+                continue
+            pl = sd.plan_attention(sd.attn_params(sd.BF16, 1, 8 * groups, groups, D, P, P, rows // 8, 1, 0))
+            q_tiles = -(-rows // pl.rows_per_workgroup)
+            assert pl.workgroups == -(-groups * pl.kv_splits // 8) * 8 * q_tiles
+            queue = -(-pl.workgroups // 256) * pl.key_tiles_per_split
+            for fewer in range(1, pl.kv_splits):
+                assert 1.25 * -(-(-(-groups * fewer // 8) * q_tiles) // 32) * -(-tiles // fewer) >= queue, (groups, tiles, fewer)
+
+
 @pytest.mark.parametrize("B,K,V,Hd", [(1, 1, 1, 32), (1, 32, 126464, 4096), (2, 32, 5000, 512), (3, 40, 777, 96),
                                        (8, 32, 126464, 4096), (16, 32, 152064, 3584), (9, 32, 700, 1024), (2, 32, 126464, 4096), (4, 32, 126464, 4096), (3, 32, 152064, 3584), (4, 32, 700, 64), (1, 32, 152064, 3584), (2, 32, 152064, 3584), (16, 4096, 100, 32)])
 def test_lm_head_plan_is_consistent(lib, B, K, V, Hd):

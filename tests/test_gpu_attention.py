@@ -283,8 +283,8 @@ def test_attention_bf16_workgroup_shapes(gpu_lib, shape, B, Hq, Hkv, D, P, cap, 
 
 @pytest.mark.parametrize("shape,rows,B,Hq,Hkv,D,P,K,S,keep", [
     (0, 64, 1, 8, 1, 128, 500, 64, 70, tuple(range(64))),                     # 1024 rows on 628 keys: 16 query tiles, splits
-    (0, 64, 2, 8, 1, 64, 700, 40, 60, tuple(range(1, 52))),                   # D = 64, 728 rows: a ragged last query tile
-    (1, 64, 1, 16, 1, 128, 900, 20, 33, tuple(range(0, 26, 2))),              # 528 rows: two groups of 64 alternate key tiles
+    (1, 64, 2, 8, 1, 64, 700, 40, 60, tuple(range(1, 52))),                   # D = 64, 728 rows, the last tile ragged, two groups alternate key tiles
+    (0, 64, 1, 16, 1, 128, 900, 20, 33, tuple(range(0, 26, 2))),              # 528 rows: nine query tiles, five splits
     (1, 128, 3, 36, 4, 128, 3000, 32, 50, tuple(range(40))),                  # 648 rows: 128-row tiles, the last with 8 rows; 16 key tiles a split
     (0, 128, 6, 64, 16, 128, 500, 64, 96, tuple(range(96))),                  # 640 rows = 5 tiles of 128, more than one round
 ])

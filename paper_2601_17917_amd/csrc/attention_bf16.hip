@@ -291,6 +291,11 @@ __device__ __forceinline__ s16x8 read_vt(const unsigned char* lds, const Lane<D>
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// 16 rows per wave: the wave that is at its P V goes first, so that the SIMD's waves drift into different phases of a tile
+// (448 rows x 1764 keys 36.9 -> 34.8 us, 384 x 560 15.3 -> 14.4; 64-wide heads and 32 rows per wave: no gain or 2-5 % slower).
+// Lowered at the start of a tile and behind the last one: epilogue and stores do not go before another workgroup's tiles.
+template <int D, int RB> constexpr bool pv_first() { return D == 128 && RB == 1; }
+
 // One key tile (ring stage STAGE, a compile-time constant so that every LDS address is base + immediate)
 template <int D, int RB, int STAGE, int NG>
 __device__ __forceinline__ void compute_tile(const AttnArgs& a, const Lane<D>& L, const unsigned char* lds, int t,
@@ -303,10 +308,7 @@ __device__ __forceinline__ void compute_tile(const AttnArgs& a, const Lane<D>& L
   // keys 269 -> 263 us; the stream-bound shapes do not notice).  Not for 64-wide heads at 32 rows per wave: 1024 rows x 2048
   // keys 168 -> 145 us without, 4 heads' 1328 rows x 3332 keys 58.0 -> 48.5.
   if constexpr (!(D == 64 && RB == 2)) __builtin_amdgcn_iglp_opt(0);
-  // 16 rows per wave: the wave that is at its P V goes first, so that the SIMD's waves drift into different phases of a tile
-  // (448 rows x 1764 keys 36.9 -> 34.8 us, 384 x 560 15.3 -> 14.4; 64-wide heads and 32 rows per wave: no gain or 2-5 % slower)
-  constexpr bool kPvFirst = (D == 128 && RB == 1);
-  if constexpr (kPvFirst) __builtin_amdgcn_s_setprio(0);
+  if constexpr (pv_first<D, RB>()) __builtin_amdgcn_s_setprio(0);
   // ---- S^T = K Q^T
   f32x4 sacc[RB][4];
 #pragma unroll
@@ -418,7 +420,7 @@ __device__ __forceinline__ void compute_tile(const AttnArgs& a, const Lane<D>& L
   }
 
   // ---- O^T += V^T P^T
-  if constexpr (kPvFirst) __builtin_amdgcn_s_setprio(1);
+  if constexpr (pv_first<D, RB>()) __builtin_amdgcn_s_setprio(1);
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
 #pragma unroll
@@ -607,6 +609,8 @@ __global__ __launch_bounds__(MODE ? 512 : 256, MODE ? 1 : 2) void attn_bf16_kern
       tile_step(std::integral_constant<int, 1>{}, t + NG + L.grp);
     }
   }
+
+  if constexpr (pv_first<D, RB>()) __builtin_amdgcn_s_setprio(0);
 
   // ---- two groups: the second hands its (O, m, l) to the first through LDS (the ring is free once every wave is
   // past its last tile); fixed order, so the result does not depend on timing

@@ -90,3 +90,13 @@ def test_projection_rows_do_not_spill(images):
                 for key in ("private_segment_fixed_size", "vgpr_spill_count", "sgpr_spill_count"):
                     assert int(re.search(r"\.%s:\s+(\d+)" % key, entry).group(1)) == 0, key
     assert seen == 2
+
+
+def test_attention_waves_lower_their_priority_again(images):
+    """The 16-row waves of 128-wide heads raise their priority at every tile's P V; what follows the last tile (merge, epilogue,
+    stores) runs at the ordinary one."""
+    kernels = {name: [s for s in ins if s.startswith("s_setprio")] for name, ins in disassembly(images, "attn_bf16_kernel").items()}
+    raised = {name: prio for name, prio in kernels.items() if prio}
+    assert len(raised) == 6 and all("ILi128ELi1E" in name for name in raised)      # every workgroup shape of <128, 1>
+    for name, prio in raised.items():
+        assert prio[-1] == "s_setprio 0", (name, prio)

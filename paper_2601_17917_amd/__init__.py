@@ -160,9 +160,12 @@ def _stream(stream):
     import torch
     if stream is not None:
         return stream.cuda_stream
-    if not torch.cuda.is_initialized():
-        return torch.cuda.current_stream().cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if torch.cuda.is_initialized():
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except (AttributeError, TypeError):               # a torch that has not got these internal calls
+            pass
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _dtype_code(t):

@@ -394,6 +394,24 @@ def test_probe_validation(lib):
     assert lib.sdllm_probe_mfma_bf16(10, 0, None, None, ctypes.byref(fl)) == sd.ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice", None])
+def test_current_stream_without_torch_internals(monkeypatch, missing):
+    """The binding takes the current stream's handle from torch's internal calls and, in a torch that has not got them, from the
+    public Stream object."""
+    import torch
+
+    class Stream:
+        cuda_stream = 1234
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 1000 + device, raising=False)
+    if missing:
+        monkeypatch.delattr(torch._C, missing)
+    assert sd._stream(None) == (1234 if missing else 1003)
+    assert sd._stream(Stream) == 1234
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,D,P,K,s", [
     (1, 1, 1, 128, 8192, 1, 0), (1, 1, 1, 64, 16, 5, 0), (3, 16, 4, 64, 1213, 27, 37), (1, 32, 32, 128, 608, 32, 32),
     (1, 32, 8, 128, 4000, 32, 32), (2, 32, 32, 128, 700, 32, 32), (10, 4, 1, 128, 1024, 256, 0), (17, 8, 2, 128, 2304, 256, 0),

@@ -326,7 +326,8 @@ __global__ __launch_bounds__(64 * f32_max_waves<NS>(), f32_max_waves<NS>() / 4) 
   int buf = 0;
   auto block = [&](int blk, auto partial) {
     if constexpr (KLDS) {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      // K of this block has landed, and the other region, which the next transfers fill, has been read
+      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
       const F32Ahead kn = f32_ahead(a, blk + a.nk);
       if (blk + a.nk < a.key_blocks) f32_dma_k<NS>(a, kk, lane, kc, kb, ks, blk + a.nk, buf ^ 1, kn);
       f32_load_v<NS>(a, l16, G, vc, vb, vs, blk, ka, v);

@@ -100,3 +100,14 @@ def test_attention_waves_lower_their_priority_again(images):
     assert len(raised) == 6 and all("ILi128ELi1E" in name for name in raised)      # every workgroup shape of <128, 1>
     for name, prio in raised.items():
         assert prio[-1] == "s_setprio 0", (name, prio)
+
+
+def test_fp32_attention_waits_for_its_lds_reads_before_it_overwrites_them(images):
+    """The transfers that bring K into LDS are inline assembly and fill the region that the block before was read from: the wait
+    in front of them names the LDS reads, whatever waits the compiler places."""
+    kernels = disassembly(images, "attention_f32_kernelILi8ELb[01]ELb1E")
+    assert len(kernels) == 2
+    for name, ins in kernels.items():
+        assert any("global_load_lds" in s for s in ins)
+        waits = [s for s in ins if s.startswith("s_waitcnt") and "vmcnt(0)" in s and "lgkmcnt(0)" in s]
+        assert len(waits) >= 2, name                     # whole blocks, and the last one that is not

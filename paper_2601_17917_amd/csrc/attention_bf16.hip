@@ -303,6 +303,11 @@ __device__ __forceinline__ void compute_tile(const AttnArgs& a, const Lane<D>& L
                                              float (&m)[RB], float (&thr)[RB], float (&lsum)[RB]) {
   using S = Shape<D, 2, NG>;
   constexpr int NS = S::NS, NDB = S::NDB;
+  // The softmax row sum.  16 rows per wave: on the matrix pipe, from the probabilities as the P V takes them, rounded to bf16, added
+  // in fp32.  32 rows per wave: fp32 probabilities on the vector ALU (the matrix pipe's sum spills there).  The rounding of
+  // numerator and denominator is the same in the former and cancels in part: over 70 problems of 512 and more rows, which the plan
+  // gives to either, with the same splits, the output's error against 64 bits is 0.84 to 1.001 of the latter's (scores of deviation
+  // 1: 0.993 in the mean, nearly even: 0.999, of deviation 4: 0.89; V shifted by 2 or 20 deviations: 0.999).
   constexpr bool kMfmaRowSum = (RB == 1);
   // the compiler's interleaving strategy for matrix instructions and LDS reads in this block (32 heads x 128, 1024 rows x 2048
   // keys 269 -> 263 us; the stream-bound shapes do not notice).  Not for 64-wide heads at 32 rows per wave: 1024 rows x 2048
@@ -787,6 +792,7 @@ AttnPlan plan_attention_bf16(const sdllm_attn_params& p) {
   // chip is idle or waits for a second round.  256 rows stay where they are within 3 % of the others (which is what the prices are
   // good for: at 950 measured problems three came out over 3 % slower than 256 rows with two workgroups' worth of splits per CU
   // took before, 14 without the margin), and below 8 key tiles.
+  // (The 64-row shape forms the softmax row sum from probabilities rounded to bf16, the others from fp32 ones: compute_tile.)
   // D 128, us, 256 rows / 128 / 64: 32 groups of 512 rows x 628 keys 23.3 / 15.8 / 11.2; 96 x 640 x 660 48.1 / 30.1 / 35.0;
   // 64 x 1024 x 1756 57.2 / 61.0 / 73.1.
   long long auto_ns = 0;

@@ -298,6 +298,29 @@ def test_attention_bf16_many_rows_few_groups(gpu_lib, shape, rows, B, Hq, Hkv, D
     assert_bf16_close(got, t, P, what=f"{rows} rows, {pl.kv_splits} split(s), {pl.key_tiles_per_split} tiles per split:")
 
 
+@pytest.mark.parametrize("spread,shift", [(1.0, 0.0), (0.1, 0.0), (2.0, 0.0), (1.0, 2.0), (1.0, 20.0)])
+@pytest.mark.parametrize("B,Hq,Hkv,D,P,K,S,keep", [
+    (1, 8, 1, 128, 500, 64, 70, tuple(range(64))),
+    (2, 8, 1, 64, 700, 40, 60, tuple(range(1, 52))),
+])
+def test_attention_bf16_row_sum_of_64_row_workgroups(gpu_lib, B, Hq, Hkv, D, P, K, S, keep, spread, shift):
+    """From 512 rows per K/V head the plan may take 64-row workgroups, whose softmax row sum adds probabilities rounded to bf16,
+    or 256-row ones, which add fp32 probabilities: the output's error against 64 bits does not grow by that.  The two differ
+    only in rounding, over B Hq (K + kept) D outputs: 1 % is ten times what their ratio exceeds 1 by at most."""
+    sd = gpu_lib
+    t = wl.make_custom_attention_inputs("bf16", B, Hq, Hkv, D, P, P, K, S, keep, seed=P + len(keep))
+    for name in ("q_block", "q_suffix", "k_cache", "k_block", "k_suffix"):
+        t[name] = wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(t[name]) * np.float32(spread))
+    for name in ("v_cache", "v_block", "v_suffix"):
+        t[name] = wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(t[name]) + np.float32(shift))
+    pl = sd.plan_attention(sd.attn_params(sd.BF16, B, Hq, Hkv, D, P, P, K, S, len(keep), 0.0, 0))
+    other = sd.plan_attention(sd.attn_params(sd.BF16, B, Hq, Hkv, D, P, P, K, S, len(keep), 0.0, pl.kv_splits))
+    assert (pl.rows_per_workgroup, other.rows_per_workgroup, other.kv_splits) == (64, 256, pl.kv_splits)
+    want = oracle(t, P)
+    error = [float(np.sqrt(((run_gpu(sd, t, P, kv_splits=n) - want) ** 2).sum())) for n in (0, pl.kv_splits)]
+    assert error[0] <= 1.01 * error[1], error
+
+
 def _random_case(seed):
     """A seeded random problem: small enough for the oracle, wide enough to reach every workgroup shape, both head
     dims, GQA ratios up to 8, empty caches / suffixes, forced and automatic key splits."""

@@ -110,9 +110,9 @@ __device__ __forceinline__ void mfma_acc(f32x4& acc, const bf16x8& a, const bf16
 }
 
 // The vocabulary tiles tile0, tile0 + tile_step, ... for one row chunk of JB 16-row blocks of positions.
-// Between its roofs: 256 positions x 126464 x 4096 take 421k cycles, of which the matrix pipe is busy 253k, at a clock that falls
-// to 2.1 GHz and below under matrix work on a full stream of W; without the transfers 389k cycles, without the matrix
-// instructions 180 us at 2.4 GHz.  What this split gains over one wave per SIMD with W straight into registers: whole
+// Between its roofs: 256 positions x 126464 x 4096 take 421k to 460k cycles by card, of which the matrix pipe is busy 253k, at a
+// clock that falls to 2.1 GHz and below under matrix work on a full stream of W; without the transfers 389k cycles, without the
+// matrix instructions 180 us at 2.4 GHz (on the card with 421k).  What this split gains over one wave per SIMD with W straight into registers: whole
 // 128-byte lines of both operands (16 rows x 64 bytes a transfer took 1.5 times as long), two waves per SIMD that fill each
 // other's gaps, one prologue per workgroup instead of one per tile.  Per call over 126464 x 4096, before / after in turn on one
 // card: row-major W 160 positions 263 / 213 us, 256: 282 / 249, 282: 412 / 313, 384: 443 / 357, 512: 503 / 454 (1.17 PFLOP/s);
@@ -1028,7 +1028,7 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_pack_kernel(const uint16_t
 // Bound by the stream of W.  A chunk is walked block by block, a block's 8 k-steps in a row: eight contiguous kilobytes at
 // a time, two such runs in flight per wave.  Walked k-step by k-step (one kilobyte of each block in turn, as many bytes in
 // flight) the blocks' starts, Hd x 32 bytes apart, met in the same memory channels where Hd is a power of two: 126464 x 4096
-// 175.6 -> 163.5 us per call with 16 masked positions, 181 -> 165 with 32 (6.8 TB/s; a plain read 7.0), 32000 x 4096 59.7 ->
+// 175.6 -> 163.5 us per call with 16 masked positions, 181 -> 165 with 32 (the kernel alone 153 us, 6.8 TB/s; a plain read 7.0), 32000 x 4096 59.7 ->
 // 53.7, 8000 x 768 21.1 -> 19.4; 152064 x 3584 170.4 and 171.1, 50257 x 1600 41.8 both.
 constexpr int kPkKS = 8;                       // k-steps per chunk of B operands
 constexpr int kPkPF = 2;                       // vocabulary blocks (chunks of 8 KB) of A operands in flight per wave
@@ -1218,9 +1218,12 @@ static int stream_tt(int V, const int (&tts)[N], int sub = kStSub) {
 
 // top: the shape for B x K positions all masked; the shapes below it are launched too and serve the smaller
 // masked counts; ntile_out is the largest tile count among the launched shapes.
-// first: the smallest shape launched.  Over a packed W the 64-position kernel streams as fast as the
-// 32-position one (161 against 167 us for 126464 x 4096), so where both would be launched the former serves
-// 1..64 masked positions and the call has one idle launch less.
+// first: the smallest shape launched.  Over a packed W, where both would be launched, the 64-position kernel serves 1..64 masked
+// positions and the call has one idle launch less.  Call with up to 32 masked of 40 to 256 positions, us, with it / with the
+// 32-position kernel launched too: 8000 x 768 16 / 16-26, 32000 x 4096 56-61 / 55-70, 50257 x 1600 39-43 / 39-50, 126464 x 2048
+// 108-116 / 112-124, 100000 x 5120 163-168 / 161-180, 152064 x 3584 173-185 / 172-182; only 126464 x 4096, where the 64-position
+// kernel's blocks start in the same memory channels, prefers the other: 175-184 / 162-172.  With 33 to 64 masked the idle launch
+// costs 1-2 % (8000 x 768: 11 %).
 struct LmPlan { int first, top, nchunk, packed, tt[kNumShapes], bn[kNumShapes], ntile[kNumShapes], ntile_out; };
 
 static LmPlan lm_plan(const sdllm_lm_head_params& p) {

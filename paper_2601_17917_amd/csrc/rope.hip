@@ -54,7 +54,8 @@ template <> struct RopeVec<uint16_t> {   // bf16 bit patterns; results rounded t
   }
 };
 
-template <typename T, bool INTERLEAVED>
+// AHEAD: a lane's first item travels while the angles are computed.  Which launches take it stands at the launch.
+template <typename T, bool INTERLEAVED, bool AHEAD>
 __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a) {
   constexpr int N = RopeVec<T>::N;
   __shared__ float cos_s[kRopeMaxHalfD], sin_s[kRopeMaxHalfD];
@@ -79,8 +80,7 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a) {
     lo = *reinterpret_cast<const u32x4*>(src + off);
     if constexpr (!INTERLEAVED) hi = *reinterpret_cast<const u32x4*>(src + off + H2);
   };
-  // the first item travels while the angles are computed (a launch of two passes at most is a chain of latencies)
-  if (tid < items) load(offset(tid));
+  if (AHEAD && tid < items) load(offset(tid));
 
   for (int i = tid; i < H2; i += 256) {
     const double theta = exp2(-(2.0 * i / D) * a.log2_base);
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a) {
 
   for (int it = tid; it < items; it += 256) {
     const long long off = offset(it);
-    if (it != tid) load(off);
+    if (!AHEAD || it != tid) load(off);
     const int first = (it % per_row) * (INTERLEAVED ? N / 2 : N);              // pair index of the vector's first pair
     if constexpr (INTERLEAVED) {
       float x[N], y[N];
@@ -120,6 +120,13 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeArgs a) {
   }
 }
 
+template <typename T>
+static void rope_launch(bool interleaved, bool ahead, dim3 grid, const RopeArgs& a, hipStream_t stream) {
+  void (*const kernel)(RopeArgs) = interleaved ? (ahead ? rope_kernel<T, true, true> : rope_kernel<T, true, false>)
+                                               : (ahead ? rope_kernel<T, false, true> : rope_kernel<T, false, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, a);
+}
+
 hipError_t launch_rope(const sdllm_rope_params& p, const void* x_block, const void* x_suffix,
                        const int32_t* keep_idx, void* out_block, void* out_suffix, hipStream_t stream) {
   RopeArgs a;
@@ -140,14 +147,16 @@ hipError_t launch_rope(const sdllm_rope_params& p, const void* x_block, const vo
   if (chunks > 65535) chunks = 65535;
   a.rows_per_chunk = (a.BH + chunks - 1) / chunks;
   chunks = (a.BH + a.rows_per_chunk - 1) / a.rows_per_chunk;
-  dim3 grid(Nq, chunks);
-  if (p.dtype == SDLLM_FP32) {
-    if (p.interleaved) hipLaunchKernelGGL((rope_kernel<float, true>), grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((rope_kernel<float, false>), grid, dim3(256), 0, stream, a);
-  } else {
-    if (p.interleaved) hipLaunchKernelGGL((rope_kernel<uint16_t, true>), grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((rope_kernel<uint16_t, false>), grid, dim3(256), 0, stream, a);
-  }
+  const dim3 grid(Nq, chunks);
+  // The first item ahead of the angles saves a round trip to memory, 0.1 to 0.4 us of a launch (q, k and the attention behind them
+  // in one graph, us less per layer: 64 rows x 32 + 32 heads x 128 0.24 of 16.5, 505 x 64 + 64 x 128 0.79 of 27.8, 64 x 832 + 208 x
+  // 64 0.55 of 20.5).  Its address arithmetic stands in front of the angles, which costs 0.1 us where the rows are few (up to 300
+  // KB), and its registers leave 5 workgroups to a CU, not 6: beyond one such round only the read of 16 MB and more hides that
+  // (2080 rows x 8 x 64 3.4 us, ahead 3.75; 2080 x 128 x 64 12.4, ahead 11.9).
+  const long long bytes = (long long)Nq * a.BH * p.D * elem;
+  const bool ahead = bytes >= 300 << 10 && ((long long)Nq * chunks <= 5 * kNumCUs || bytes >= 16 << 20);
+  if (p.dtype == SDLLM_FP32) rope_launch<float>(p.interleaved != 0, ahead, grid, a, stream);
+  else rope_launch<uint16_t>(p.interleaved != 0, ahead, grid, a, stream);
   return hipGetLastError();
 }
 

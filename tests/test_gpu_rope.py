@@ -67,6 +67,22 @@ def test_rope_shapes(gpu_lib, dtype, interleaved, B, H, D, K, S, keep, pos0, bas
     _check(gpu_lib, dtype, B, H, D, K, S, keep, pos0, base, interleaved, in_place=True, seed=D + K + 1)
 
 
+@pytest.mark.parametrize("dtype,B,H,D,rows", [
+    ("bf16", 2, 4, 128, 149), ("bf16", 2, 4, 128, 150),           # 300 KB of rows
+    ("fp32", 1, 7, 80, 137), ("fp32", 1, 7, 80, 138),
+    ("bf16", 1, 2, 128, 1280), ("bf16", 1, 2, 128, 1281),         # one round of five workgroups per CU
+    ("bf16", 4, 8, 128, 2047), ("bf16", 4, 8, 128, 2048),         # 16 MB
+    ("fp32", 3, 41, 64, 600),                                     # a workgroup's last pass not full
+])
+@pytest.mark.parametrize("interleaved", [False, True])
+def test_rope_first_item_ahead_of_the_angles(gpu_lib, dtype, interleaved, B, H, D, rows):
+    """A lane's first item is loaded before the angles are known in launches of some size: on both sides of every line of that
+    rule, out of place and in place."""
+    keep = np.arange(3, 3 + rows - 32)
+    for in_place in (False, True):
+        _check(gpu_lib, dtype, B, H, D, 32, rows + 5, keep, 700, 500000.0, interleaved, in_place, seed=rows + D)
+
+
 def test_rope_cfg2_shape_q_and_k(gpu_lib):
     """The bench workload's shapes: 32 query heads, the paper-rule keep list (31 nearest + trailing)."""
     w = wl.WORKLOADS["cfg2"]

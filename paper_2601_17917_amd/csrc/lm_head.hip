@@ -1073,7 +1073,11 @@ __global__ __launch_bounds__(kLmThreads) void lm_head_packed_kernel(LmHeadArgs a
   const int NCH = (NK + kPkKS - 1) / kPkKS;        // chunks
   const int NB = (a.V + 15) / 16;                  // 16-row blocks of the image
   const int q = lane >> 4, l16 = lane & 15;
-  const int c0 = tile % NCH;                       // this workgroup's rotation of the chunk order
+  // This workgroup's rotation of the chunk order.  With exactly eight chunks, blocks 64 KB apart, tile % NCH would be the number of
+  // the chip part and all of its workgroups would read the same columns at a time: 126464 x 2048 112 -> 91 us per call, 100000 x 2048
+  // 106 -> 76, 152064 and 32000 rows level (walked k-step by k-step, 100 and 98).  Other widths of eight chunks, whose blocks do
+  // not start on the same address bits, are level or up to 7 % slower that way, and so is 1024 with its four chunks.
+  const int c0 = (NK == kNumXCDs * kPkKS ? tile >> 3 : tile) % NCH;
   auto chunk_at = [&](int c) { int ch = min(c, NCH - 1) + c0; return ch - ((ch >= NCH) ? NCH : 0); };
   // A operands: block nb0 + t of the image, this lane's 16 bytes of every k-step 512 elements apart
   const int nb0 = (tile * kLmWaves + wave) * TT;

@@ -220,6 +220,18 @@ def test_lm_head_rows_walk_several_tiles(gpu_lib, n_masked, Hd, packed):
     assert skipped <= 1
 
 
+@pytest.mark.parametrize("Hd", [1792, 1824, 2016, 2048, 2080])
+@pytest.mark.parametrize("V", [1500, 9000])
+def test_lm_head_packed_rotation_of_the_chunks(gpu_lib, V, Hd):
+    """At most 32 positions over a packed weight: seven, eight and nine chunks of k-steps, full and not, and the width at which
+    the rotation starts by another rule; 24 and 141 workgroups."""
+    B, K = 1, 32
+    h, W, tokens, masked, hd, Wd = _host_case(B, K, Hd, V, seed=V + Hd, frac=0.8)
+    got = run_gpu(gpu_lib, hd, Wd, tokens, masked, 0.5, 0.3, packed=True)
+    n_gap, n_band, skipped = compare(got, _oracle(h, W, tokens, masked, 0.5, 0.3), tokens, masked)
+    assert skipped == 0
+
+
 @pytest.mark.parametrize("B,K,n_masked,V", [
     (5, 64, 192, 67100), (5, 64, 224, 67100),                 # chunks of 192 and 224 rows that walk two or three tiles
     (12, 64, 700, 67100),                                     # three chunks: nine workgroups each per XCD, 33 tiles to share out

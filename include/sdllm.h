@@ -90,7 +90,9 @@ typedef struct sdllm_attn_params {
 } sdllm_attn_params;
 
 /* Bytes of device workspace sdllm_block_attention needs for these parameters (0 if none);
- * (size_t)-1 if the parameters are invalid. */
+ * (size_t)-1 if the parameters are invalid.  With automatic splits the need does not only grow with prefix_len (a longer
+ * sequence may take fewer splits): a workspace kept over a generation is sized by the largest need along it, or asked for
+ * again before each call. */
 size_t sdllm_attention_workspace_bytes(const sdllm_attn_params* p);
 
 /*

@@ -417,8 +417,9 @@ def test_current_stream_without_torch_internals(monkeypatch, missing):
     (1, 32, 8, 128, 4000, 32, 32), (2, 32, 32, 128, 700, 32, 32), (10, 4, 1, 128, 1024, 256, 0), (17, 8, 2, 128, 2304, 256, 0),
     (7, 32, 16, 128, 900, 64, 0), (16, 28, 4, 128, 512, 32, 32), (8, 32, 32, 128, 1024, 32, 992), (16, 64, 32, 64, 8192, 8, 0)])
 def test_attention_automatic_splits(lib, B, Hq, Hkv, D, P, K, s):
-    """No split from one workgroup per CU on; below that the longest chain of key tiles of a CU never grows by splitting, and
-    8-wave workgroups with rows of their own (shape 2) never start a second round."""
+    """On these problems, from a single workgroup to several per CU: no split from one workgroup per CU on; below that the longest
+    chain of key tiles of a CU, by workgroups over all CUs, does not grow by splitting, 8-wave workgroups with rows of their own
+    (shape 2) start no second round, and a few workgroups on a long sequence are split."""
     def plan(splits):
         return sd.plan_attention(sd.attn_params(sd.BF16, B, Hq, Hkv, D, P, P, K, max(s, 1), s, 0.0, splits))
     auto = plan(0)
